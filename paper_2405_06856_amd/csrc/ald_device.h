@@ -94,35 +94,29 @@ __device__ __forceinline__ bool ranks_before(uint64_t ka, int a, uint64_t kb, in
     return (a >= 0) & ((b < 0) | better);
 }
 
-// Insert candidate (ck, cw) into a best-first list of N entries (cw < 0: no-op).
-// Written as a compare-exchange chain of selects: no divergent branch touches
-// the register-resident list.
-template <int N>
-__device__ __forceinline__ void topk_insert(uint64_t (&key)[N], int32_t (&idx)[N], uint64_t ck, int32_t cw)
+// Two smallest KV excesses of a query as packed keys: excess (offset to
+// unsigned) in the high word, the complement of the worker index in the low
+// word -- smaller key = smaller excess, then higher index (the order the
+// commit's tie rule expects).  ~0 marks an empty entry.
+__device__ __forceinline__ uint64_t ex_key(int32_t ex, int32_t w)
 {
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-        const bool sw = ranks_before(ck, cw, key[k], idx[k]);
-        const uint64_t ok = key[k];
-        const int32_t ow = idx[k];
-        key[k] = sw ? ck : ok;
-        idx[k] = sw ? cw : ow;
-        ck = sw ? ok : ck;
-        cw = sw ? ow : cw;
-    }
+    return ((uint64_t)((uint32_t)ex ^ 0x80000000u) << 32) | (uint32_t)~(uint32_t)w;
+}
+__device__ __forceinline__ void ex_unpack(uint64_t k, int32_t& ex, int32_t& w)
+{
+    ex = k == ~0ull ? INT32_MAX : (int32_t)((uint32_t)(k >> 32) ^ 0x80000000u);
+    w = k == ~0ull ? -1 : (int32_t)~(uint32_t)k;
 }
 
-// Keep the two smallest (excess, index) pairs, ordered by excess ascending and
-// then index descending.  y < 0: no candidate.
-__device__ __forceinline__ void min2_insert(int32_t& ex1, int32_t& w1, int32_t& ex2, int32_t& w2, int32_t x, int32_t y)
+// The two smallest keys of two pairs of the two smallest (new first = smaller
+// first; new second = min(larger first, smaller second)).
+__device__ __forceinline__ void merge_two(uint64_t& a1, uint64_t& a2, uint64_t b1, uint64_t b2)
 {
-    const bool present = y >= 0;
-    const bool b1 = present & ((w1 < 0) | (x < ex1) | ((x == ex1) & (y > w1)));
-    const bool b2 = present & !b1 & ((w2 < 0) | (x < ex2) | ((x == ex2) & (y > w2)));
-    ex2 = b1 ? ex1 : (b2 ? x : ex2);
-    w2 = b1 ? w1 : (b2 ? y : w2);
-    ex1 = b1 ? x : ex1;
-    w1 = b1 ? y : w1;
+    const uint64_t lo = b1 < a1 ? b1 : a1;
+    const uint64_t hi = b1 < a1 ? a1 : b1;
+    const uint64_t s2 = b2 < a2 ? b2 : a2;
+    a1 = lo;
+    a2 = hi < s2 ? hi : s2;
 }
 
 __device__ __forceinline__ bool near_tie(double x, double y)
@@ -247,32 +241,41 @@ __device__ int64_t wave_last_true(int64_t lo, int64_t hi, F pred)
     return a;
 }
 
+// The same, starting from an estimate: the lanes test the 64 points around it,
+// and the search runs only where the answer is not among them.
+template <typename F>
+__device__ int64_t wave_last_true_near(double est, int64_t lo, int64_t hi, F pred)
+{
+    const int64_t a = (int64_t)fmax((double)lo, fmin((double)hi, est)) - 32;  // (a NaN estimate: hi)
+    const int64_t x = a + lane_id();
+    const uint64_t m = ballot(x < lo || (x <= hi && pred(x)));
+    if ((m & 1) && m != ~0ull) return a + __popcll(m) - 1;  // (pred holds on a prefix)
+    return wave_last_true(lo, hi, pred);
+}
+
 // Half-width of an interval around y that holds every x with near_tie(x, y):
 // near_tie gives |x - y| <= 1e-9 max(|x|, |y|) up to rounding, which implies
 // |x - y| < 1.0000002e-9 |y|; the extra 25% covers the rounding of y +- width.
 __device__ __forceinline__ double tie_band(double y) { return 1.25e-9 * fabs(y); }
 
-// Scenario owning block `blk` given each scenario's first block (field offset).
+// The last scenario whose `FIRST` field (a first block or first worker, rising
+// over the scenarios) is at most x.  Every lane of the wave must call it with the
+// same x: the lanes test 64 evenly spaced scenarios per step, so 64 scenarios
+// take one round trip and 4,096 two.
 template <int32_t Scen::*FIRST>
-__device__ __forceinline__ int find_scen(const State& st, int blk)
+__device__ __forceinline__ int find_scen(const State& st, int x)
 {
-    int lo = 0, hi = st.S - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (st.scen[mid].*FIRST <= blk) lo = mid; else hi = mid - 1;
+    int lo = 0, n = st.S;  // the answer lies in [lo, lo + n)
+    while (n > 1) {
+        const int step = (n + 63) >> 6, k = lane_id() * step;
+        const bool at = k < n && st.scen[lo + k].*FIRST <= x;
+        const int cnt = __popcll(__builtin_amdgcn_ballot_w64(at));
+        lo += (cnt - 1) * step;
+        n = min(step, n - (cnt - 1) * step);
     }
     return lo;
 }
-
-__device__ __forceinline__ int find_scen_by_worker(const State& st, int gw)
-{
-    int lo = 0, hi = st.S - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (st.scen[mid].wbase <= gw) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
+__device__ __forceinline__ int find_scen_by_worker(const State& st, int gw) { return find_scen<&Scen::wbase>(st, gw); }
 
 __device__ __forceinline__ void raise_error(int32_t* err, int32_t code)
 {
@@ -280,6 +283,11 @@ __device__ __forceinline__ void raise_error(int32_t* err, int32_t code)
 }
 
 // ---- cross-lane primitives (readlane and DPP; no LDS permutes)
+
+// LLVM's writelane intrinsic (v_writelane_b32): the value of lane `lane` of
+// `old` replaced by the wave-uniform `v`.  Through the intrinsic the compiler
+// sees the instruction and inserts whatever wait states its operands need.
+__device__ int ald_writelane(int v, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
 
 // Read a lane's value (uniform result).
 __device__ __forceinline__ int32_t rdlane(int32_t v, int l) { return __builtin_amdgcn_readlane(v, l); }
@@ -322,27 +330,12 @@ struct Min32 {
 };
 __device__ __forceinline__ int32_t wave_sum32(int32_t v) { return rdlane(wave_incl_scan(v, 0, Add32()), 63); }
 __device__ __forceinline__ int32_t wave_min32(int32_t v) { return rdlane(wave_incl_scan(v, INT32_MAX, Min32()), 63); }
-// Largest 64-bit unsigned value over the 64 lanes: the same scan on both
-// halves of the word, the comparison on the whole word.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ uint64_t dpp_u64(uint64_t ident, uint64_t x)
+struct MaxU32 {
+    __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return a > b ? a : b; }
+};
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
 {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)ident, (int)(uint32_t)x, CTRL, ROW_MASK,
-                                                              0xf, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(ident >> 32), (int)(uint32_t)(x >> 32),
-                                                              CTRL, ROW_MASK, 0xf, false);
-    return ((uint64_t)hi << 32) | lo;
-}
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t x)
-{
-    auto mx = [](uint64_t a, uint64_t b) { return a > b ? a : b; };
-    x = mx(x, dpp_u64<0x111, 0xf>(0, x));  // row_shr:1
-    x = mx(x, dpp_u64<0x112, 0xf>(0, x));  // row_shr:2
-    x = mx(x, dpp_u64<0x114, 0xf>(0, x));  // row_shr:4
-    x = mx(x, dpp_u64<0x118, 0xf>(0, x));  // row_shr:8
-    x = mx(x, dpp_u64<0x142, 0xa>(0, x));  // row_bcast:15
-    x = mx(x, dpp_u64<0x143, 0xc>(0, x));  // row_bcast:31
-    return rdlane64(x, 63);
+    return (uint32_t)rdlane((int32_t)wave_incl_scan((int32_t)v, 0, MaxU32()), 63);
 }
 __device__ __forceinline__ int32_t wave_max32(int32_t v) { return rdlane(wave_incl_scan(v, INT32_MIN, Max32()), 63); }
 __device__ __forceinline__ uint64_t wave_or64(uint64_t v)
@@ -350,6 +343,16 @@ __device__ __forceinline__ uint64_t wave_or64(uint64_t v)
     const uint32_t lo = (uint32_t)rdlane((int32_t)wave_incl_scan((int32_t)(uint32_t)v, 0, Or32()), 63);
     const uint32_t hi = (uint32_t)rdlane((int32_t)wave_incl_scan((int32_t)(uint32_t)(v >> 32), 0, Or32()), 63);
     return ((uint64_t)hi << 32) | lo;
+}
+// Largest value over this lane and those above it.
+__device__ __forceinline__ int32_t wave_suffix_max(int32_t x)
+{
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int32_t o = __shfl_down(x, d, 64);
+        x = lane_id() + d < 64 ? (x > o ? x : o) : x;
+    }
+    return x;
 }
 __device__ __forceinline__ int64_t wave_sum64(int64_t v)
 {

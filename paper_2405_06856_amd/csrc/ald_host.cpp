@@ -35,15 +35,16 @@ struct Arena {
     int32_t S = 0, NW = 0;
     int32_t T = 0;            // tile the scratch is laid out for
     int32_t target = 0;       // and the evaluation grid it aimed at
-    int32_t eval_blocks = 0, sel_blocks = 0, commit_blocks = 0;
+    int32_t eval_blocks = 0, sel_blocks = 0;
     char* scratch = nullptr;  // where the tile scratch was laid out (in the call part of the workspace)
     Scen* dscen = nullptr;
     int eval_mode = 2;    // how the pair evaluation takes the latency checks (launch_eval)
     bool use_d = false;   // some scenario checks constraint (d)
-    // the commit keeps its untouched-worker scan's rows and keys in LDS: one
-    // scenario of at most COMMIT_CACHE_W workers whose tiles heartbeats cut
-    // (short tiles whose queries commit, so that scans repeat within a window)
-    bool commit_cache = false;
+    int64_t any_words = 0;  // group words of every scenario (State::any)
+    bool small = false;     // no worker has more than SMALL_SLOTS slots
+    // BUILT_* that every built worker has (a call that needs more checks every
+    // worker first)
+    int32_t have = 0;
     Ctl* hctl = nullptr;  // pinned host copy of the control blocks
     int32_t hctl_n = 0;
     // per scenario: the host copy of its per-query heartbeats during a call
@@ -258,10 +259,10 @@ int make_arena(ald_handle* h, Arena* a, const std::vector<Scen>& scen, const std
     for (const Scen& x : scen) use_d = use_d || x.use_d;
     const int64_t log_slots = use_d ? slots : 1;
     auto carve = [&](Carver& c) {
-        c.take(&st.slot_base, NW); c.take(&st.cap, NW); c.take(&st.n, NW); c.take(&st.head, NW);
+        c.take(&st.slot_base, NW); c.take(&st.cap, NW); c.take(&st.n, NW); c.take(&st.head, NW); c.take(&st.tn, NW);
         c.take(&st.M, NW); c.take(&st.S1, NW); c.take(&st.S2, NW); c.take(&st.hbs, NW);
         c.take(&st.built, NW); c.take(&st.B, NW); c.take(&st.DS, NW); c.take(&st.key, NW);
-        c.take(&st.peak, NW); c.take(&st.rhs, NW); c.take(&st.SC, NW); c.take(&st.SR, NW);
+        c.take(&st.peak, NW); c.take(&st.peake, NW); c.take(&st.rhs, NW); c.take(&st.SC, NW); c.take(&st.SR, NW);
         c.take(&st.dq_max, NW); c.take(&st.ntd_lo, NW); c.take(&st.ntd_hi, NW);
         c.take(&st.lthr, NW); c.take(&st.ntt_lo, NW); c.take(&st.ntt_hi, NW);
         c.take(&st.ntd_mask, NW); c.take(&st.ntt_mask, NW);
@@ -309,6 +310,8 @@ int make_arena(ald_handle* h, Arena* a, const std::vector<Scen>& scen, const std
     }
     a->eval_mode = ntint ? 2 : (mono ? 1 : 0);
     a->use_d = use_d;
+    a->small = *std::max_element(caps.begin(), caps.end()) <= SMALL_SLOTS;
+    a->have = 0;
     // empty workers of a scenario are interchangeable when they share one capacity
     int64_t w0 = 0;
     for (int s = 0; s < a->S; ++s) {
@@ -329,7 +332,8 @@ int layout_scratch(ald_handle* h, Arena* a, int32_t T, int32_t target_blocks, ch
     // SEL_THREADS queries; bit words: one per 64 queries and worker
     const int32_t echunks = (T + EVAL_Q - 1) / EVAL_Q;
     const int32_t schunks = (T + SEL_THREADS - 1) / SEL_THREADS;
-    const int64_t groups = (int64_t)echunks * (EVAL_Q / 64);
+    const bool brief = T <= SHORT_TILE;
+    const int64_t groups = brief ? (T + 63) / 64 : (int64_t)echunks * (EVAL_Q / 64);
     int64_t NWtot = 0;
     for (int s = 0; s < a->S; ++s) NWtot += a->hW[s];
     int32_t Wmax = 1;
@@ -340,47 +344,59 @@ int layout_scratch(ald_handle* h, Arena* a, int32_t T, int32_t target_blocks, ch
     // evaluation's extra blocks outweigh the longer merge up to about there)
     wpb = std::max(wpb, (Wmax + 511) / 512);
     wpb = std::min(wpb, EVAL_WPB_MAX);
-    int64_t bits = 0, part = 0, qs = 0;
-    int32_t eb = 0, sb = 0, cb = 0;
+    // short tiles: blocks of one 64-query group.  A block's time is its dependent
+    // reads, so few workers each, while there are blocks enough for about
+    // eight per compute unit; and at most 128 worker blocks per scenario, whose
+    // results the commit merges per query
+    if (brief) {
+        wpb = 16;
+        while (wpb < SHORT_WPB && NWtot * groups > (int64_t)wpb * 2048) wpb *= 2;
+        wpb = std::max(wpb, std::min((Wmax + 127) / 128, SHORT_WPB));
+    }
+    int64_t bits = 0, part = 0, qs = 0, any = 0;
+    int32_t eb = 0, sb = 0;
     std::vector<Scen> hs = a->hscen;  // the arena changes only when the layout is placed
     for (int s = 0; s < a->S; ++s) {
         Scen& sc = hs[s];
         sc.wpb = std::min(wpb, std::max(1, sc.W));
         sc.nblk = (sc.W + sc.wpb - 1) / sc.wpb;
         sc.eval_blk0 = eb;
-        eb += sc.nblk * echunks;
+        eb += sc.nblk * (brief ? (int32_t)groups : echunks);
         sc.sel_blk0 = sb;
         // waves per 64-query group: more for wide scenarios, whose per-query
         // scan over workers is long
         sc.sel_g = sc.W >= 2048 ? 4 : (sc.W >= 1024 ? 2 : 1);
         const int32_t qgroups = (T + 63) / 64;
         const int32_t per_blk = (SEL_THREADS / 64) / sc.sel_g;
-        sb += (qgroups + per_blk - 1) / per_blk;
-        sc.fin_blk0 = cb;
-        cb += 1;
+        sc.sel_n = (qgroups + per_blk - 1) / per_blk;
+        sb += sc.sel_n;
         sc.bits_off = bits;
         bits += groups * sc.W;
         sc.part_off = part;
-        sc.pstride = (int64_t)echunks * EVAL_Q;
-        part += sc.pstride * sc.nblk;
+        sc.pstride = brief ? groups * 64 : (int64_t)echunks * EVAL_Q;
+        part += sc.pstride * sc.nblk * (brief ? 2 : 1);
         sc.qsum_off = qs;
         qs += (int64_t)schunks * SEL_THREADS;
+        sc.any_off = any;
+        any += groups;
     }
     // one-scenario tiles this long are evaluated in l_pred order: the tile's
     // permutation and its inverse
     const bool sorted = a->S == 1 && T >= SORT_MIN_TILE;
     const size_t perm_bytes = sorted ? align256((size_t)echunks * EVAL_Q * sizeof(int32_t)) : 0;
-    *bytes = align256((size_t)bits * 16 + (size_t)part * sizeof(ulonglong2) + (size_t)qs * sizeof(QSum) + 1024) +
+    *bytes = align256((size_t)bits * 16 + (size_t)part * sizeof(ulonglong2) + (size_t)qs * sizeof(QSum) +
+                      (size_t)any * 8 + (size_t)NWtot * sizeof(int32_t) + 2048) +
              2 * perm_bytes;
     if (!base) return ALD_OK;
     a->hscen = hs;
     a->eval_blocks = eb;
     a->sel_blocks = sb;
-    a->commit_blocks = cb;
+    a->any_words = any;
     a->T = T;
     a->target = target_blocks;
     a->scratch = base;
     char* p = base;
+    a->st.brief = brief ? 1 : 0;
     a->st.bits_feas = (uint64_t*)p;
     p += (size_t)bits * 8;
     a->st.bits_nt = (uint64_t*)p;
@@ -391,6 +407,12 @@ int layout_scratch(ald_handle* h, Arena* a, int32_t T, int32_t target_blocks, ch
     p = (char*)(((uintptr_t)p + 255) & ~(uintptr_t)255);
     a->st.qsum = (QSum*)p;
     p += (size_t)qs * sizeof(QSum);
+    p = (char*)(((uintptr_t)p + 255) & ~(uintptr_t)255);
+    a->st.any = (uint64_t*)p;
+    p += (size_t)any * 8;
+    p = (char*)(((uintptr_t)p + 255) & ~(uintptr_t)255);
+    a->st.order = (int32_t*)p;
+    p += (size_t)NWtot * sizeof(int32_t);
     p = (char*)(((uintptr_t)p + 255) & ~(uintptr_t)255);
     a->st.qorig = sorted ? (int32_t*)p : nullptr;
     a->st.qpos = sorted ? (int32_t*)(p + perm_bytes) : nullptr;
@@ -463,8 +485,8 @@ void relocate(Arena* a, const char* from, size_t n, ptrdiff_t d)
         if (p != nullptr && c >= from && c < from + n) p = (std::remove_reference_t<decltype(p)>)(c + d);
     };
     State& st = a->st;
-    mv(st.slot_base); mv(st.cap); mv(st.n); mv(st.head); mv(st.M); mv(st.S1); mv(st.S2); mv(st.hbs);
-    mv(st.built); mv(st.B); mv(st.DS); mv(st.key); mv(st.peak); mv(st.rhs); mv(st.SC); mv(st.SR);
+    mv(st.slot_base); mv(st.cap); mv(st.n); mv(st.head); mv(st.tn); mv(st.M); mv(st.S1); mv(st.S2); mv(st.hbs);
+    mv(st.built); mv(st.B); mv(st.DS); mv(st.key); mv(st.peak); mv(st.peake); mv(st.rhs); mv(st.SC); mv(st.SR);
     mv(st.dq_max); mv(st.ntd_lo); mv(st.ntd_hi); mv(st.lthr); mv(st.ntt_lo); mv(st.ntt_hi);
     mv(st.ntd_mask); mv(st.ntt_mask); mv(st.phi); mv(st.phi_hb); mv(st.dlim); mv(st.ntp_lo); mv(st.ntp_hi);
     mv(st.lgn); mv(st.lge); mv(st.lgw); mv(st.lgs); mv(st.e); mv(st.s); mv(st.pms); mv(st.lbt);
@@ -489,6 +511,18 @@ int32_t next_hb(const int32_t* hb, int32_t from, int32_t Q)
     int32_t j = from + 1;
     while (j < Q && hb[j] == 0) ++j;
     return j;
+}
+
+// The most queries between two heartbeats (no tile is longer).
+int32_t longest_window(const int32_t* hb, int32_t Q)
+{
+    int32_t most = 1, from = 0;
+    for (int32_t q = 1; q <= Q; ++q)
+        if (q == Q || hb[q] > 0) {
+            most = std::max(most, q - from);
+            from = q;
+        }
+    return most;
 }
 
 // Rounds needed to finish every scenario from its control state, if no tile
@@ -539,13 +573,20 @@ int ensure_hctl(ald_handle* h, Arena* a)
     return ALD_OK;
 }
 
+// What the rounds of a call need of the workers' summaries.
+int32_t built_need(const Arena* a)
+{
+    return BUILT_BASE | (a->st.brief ? 0 : BUILT_TABLE) | (a->st.out_diag != nullptr ? BUILT_TIES : 0);
+}
+
 // One round of the tile pipeline on every scenario of the arena.
 int launch_round(ald_handle* h, Arena* a, int mode)
 {
-    if (mode >= 0) LAUNCH(h, 0, launch_build(a->st, h->stream, mode));
+    const int32_t need = built_need(a);
+    if (mode >= 0) LAUNCH(h, 0, launch_build(a->st, h->stream, mode, need, a->small));
     LAUNCH(h, 1, launch_eval(a->st, a->eval_blocks, a->eval_mode, h->stream));
-    LAUNCH(h, 2, launch_select(a->st, a->sel_blocks, h->stream));
-    LAUNCH(h, 3, launch_commit(a->st, a->commit_blocks, a->use_d, a->commit_cache, h->stream));
+    if (a->st.out_diag != nullptr && !a->st.brief) LAUNCH(h, 2, launch_select(a->st, a->sel_blocks, h->stream));
+    LAUNCH(h, 3, launch_commit(a->st, a->S, a->use_d, h->stream));
     return ALD_OK;
 }
 
@@ -645,6 +686,8 @@ int settle(ald_handle* h, bool resume)
     }
     const AsyncCall x = h->issued[k];
     const bool last = k + 1 == h->issued.size();
+    // (calls that did not run have built nothing: the next one checks every worker)
+    if (c.err || c.start < c.Q || !last) a->have = 0;
     if (c.err) {
         h->issued.clear();
         set_pos(h, x.before);
@@ -666,7 +709,7 @@ int settle(ald_handle* h, bool resume)
         a->st.out_worker = x.st.out_worker;
         a->st.out_diag = x.st.out_diag;
         a->st.call = x.call;
-        a->commit_cache = x.moves && a->S == 1 && a->hW[0] <= COMMIT_CACHE_W;
+        HIPCHK(h, launch_clear(a->st.any, a->any_words, h->stream));
         std::vector<Ctl> hc(1, c);
         rc = run_rounds(h, a, x.moves, x.moves ? 0 : 1, hc);
         if (rc != ALD_OK) {
@@ -923,7 +966,8 @@ int load_workers(ald_handle_t h, int32_t W, const ald_model_t* model, const int6
     c.rebuild = 1;
     c.first_rej = INT32_MAX;
     HIPCHK(h, hipMemcpyAsync(a->st.ctl, &c, sizeof(Ctl), hipMemcpyHostToDevice, h->stream));
-    HIPCHK(h, launch_build(a->st, h->stream, 0));
+    HIPCHK(h, launch_build(a->st, h->stream, 0, BUILT_BASE | BUILT_TABLE | BUILT_TIES, a->small));
+    a->have = BUILT_BASE | BUILT_TABLE | BUILT_TIES;
     HIPCHK(h, hipMemcpyAsync(&c, a->st.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, h->stream));
     HIPCHK(h, hipStreamSynchronize(h->stream));
     if (c.err) { delete a; return map_dev_error(h, c.err); }
@@ -1020,6 +1064,7 @@ int place_stream(ald_handle_t h, int32_t Q, const int32_t* q_l_in, const int32_t
     Arena* a = h->main;
     int32_t T = std::min(h->tile, Q);
     if (H > 0) T = std::min(T, H);
+    if (hb_before) T = std::min(T, longest_window(hb_before, Q));
     const int32_t wave = h->eval_wave[a->eval_mode][out_diag ? 1 : 0];
     // the call part of the workspace: the tile scratch, then the per-query heartbeats
     char* const call = h->ws + h->state_bytes;
@@ -1060,8 +1105,8 @@ int place_stream(ald_handle_t h, int32_t Q, const int32_t* q_l_in, const int32_t
     // an asynchronous call after another one starts only if that one finished
     const int32_t gate = (async && !h->issued.empty()) ? h->issued.back().call : -1;
     TileInfo ti{};
-    ti.first_pc[0] = ti.first_pc[1] = INT32_MAX;
-    HIPCHK(h, launch_begin(c, ti, a->st.ctl, a->st.tinfo, a->st.qbad, gate, h->stream));
+    ti.first_pc = ti.empty_rank = INT32_MAX;
+    HIPCHK(h, launch_begin(c, ti, a->st.ctl, a->st.tinfo, a->st.qbad, gate, a->st.any, a->any_words, h->stream));
     a->st.q_lin = q_l_in;
     a->st.q_lpred = q_l_pred;
     a->st.out_worker = out_worker;
@@ -1071,9 +1116,12 @@ int place_stream(ald_handle_t h, int32_t Q, const int32_t* q_l_in, const int32_t
     // first build: every worker after a heartbeat, the last commit round's
     // workers if it changed any (unknown after an asynchronous call), else nothing
     const bool moves = H > 0 || hb_before != nullptr;  // heartbeats can move tau within the call
-    a->commit_cache = moves && a->S == 1 && a->hW[0] <= COMMIT_CACHE_W;
     const bool dirty = h->dirty_pending || !h->issued.empty();
-    const int first_mode = (rebuild || moves || h->check_all) ? 0 : (dirty ? 1 : -1);
+    const bool lacks = (built_need(a) & ~a->have) != 0;
+    const int first_mode = (rebuild || moves || h->check_all || lacks) ? 0 : (dirty ? 1 : -1);
+    // what a first round that checks every worker adds, and no more than later
+    // rounds build
+    a->have = built_need(a) & (first_mode == 0 ? ~0 : a->have);
     if (async) {
         rc = ensure_hctl(h, a);
         if (rc != ALD_OK) return rc;
@@ -1292,6 +1340,7 @@ int grouped_view(ald_handle* h, int32_t G, const int32_t* sizes, char* base, siz
     }
     a.eval_mode = m->eval_mode;
     a.use_d = m->use_d;
+    a.small = m->small;
     a.st = m->st;  // worker and slot arrays
     a.st.call = 0;  // as in its own control blocks
     Carver c{nullptr};
@@ -1392,7 +1441,13 @@ int ald_place_grouped(ald_handle_t h, int32_t G, const int32_t* group_workers, i
     // maps and heartbeat counts, then the tile scratch
     int32_t qmax = 1;
     for (int32_t g = 0; g < G; ++g) qmax = std::max(qmax, off[g + 1] - off[g]);
-    const int32_t T = std::min(h->tile, qmax);
+    int32_t T = std::min(h->tile, qmax);
+    if (H > 0) {  // no tile of a group is longer than its longest heartbeat window
+        int32_t most = 1;
+        for (int32_t g = 0; g < G; ++g)
+            if (off[g + 1] > off[g]) most = std::max(most, longest_window(hbq + off[g], off[g + 1] - off[g]));
+        T = std::min(T, most);
+    }
     const int32_t wave = h->eval_wave[h->main->eval_mode][out_diag ? 1 : 0];
     size_t vb = 0, sbytes = 0;
     int rc = grouped_view(h, G, group_workers, nullptr, &vb);
@@ -1439,7 +1494,7 @@ int ald_place_grouped(ald_handle_t h, int32_t G, const int32_t* group_workers, i
     rc = layout_scratch(h, &a, T, wave, call + vb + tb, &sbytes);  // also copies the scenario table
     if (rc != ALD_OK) return rc;
     std::vector<TileInfo> ti(G);
-    for (auto& t : ti) { t = TileInfo{}; t.first_pc[0] = t.first_pc[1] = INT32_MAX; }
+    for (auto& t : ti) { t = TileInfo{}; t.first_pc = t.empty_rank = INT32_MAX; }
     HIPCHK(h, hipMemcpyAsync(a.st.ctl, c.data(), G * sizeof(Ctl), hipMemcpyHostToDevice, h->stream));
     HIPCHK(h, hipMemcpyAsync(a.st.tinfo, ti.data(), G * sizeof(TileInfo), hipMemcpyHostToDevice, h->stream));
     a.st.q_lin = q_l_in;
@@ -1447,7 +1502,9 @@ int ald_place_grouped(ald_handle_t h, int32_t G, const int32_t* group_workers, i
     a.st.out_worker = out_worker;
     a.st.out_diag = (Diag*)out_diag;
     a.st.err_word = nullptr;
+    HIPCHK(h, launch_clear(a.st.any, a.any_words, h->stream));
     HIPCHK(h, launch_query_stats(q_l_in, q_l_pred, Q, a.st.ctl, G, h->stream));
+    h->main->have &= built_need(&a);
     rc = run_rounds(h, &a, H > 0, 0, c);
     if (rc != ALD_OK) return rc;
     // the stream's clock after the call; heartbeats after a group's last query
@@ -1683,7 +1740,12 @@ int sweep(ald_handle_t h, int32_t S, const ald_scenario_t* scen, const int32_t* 
     // the call part of the workspace: every scenario's workers, then the tile scratch
     if (!h->sweep) h->sweep = new Arena();
     Arena& a = *h->sweep;
-    const int32_t T = std::max(1, std::min(h->tile, Q));
+    int32_t T = std::max(1, std::min(h->tile, Q));
+    if (any_hb) {  // no tile is longer than its scenario's heartbeat period
+        int32_t most = 1;
+        for (int32_t s = 0; s < S; ++s) most = std::max(most, H[s] > 0 ? std::min(H[s], T) : T);
+        T = most;
+    }
     size_t ab = 0, sbytes = 0;
     int rc = make_arena(h, &a, sc, W, caps, Ms, nullptr, &ab);
     if (rc == ALD_OK) rc = layout_scratch(h, &a, T, 16384, nullptr, &sbytes);
@@ -1708,7 +1770,7 @@ int sweep(ald_handle_t h, int32_t S, const ald_scenario_t* scen, const int32_t* 
         c[s].first_rej = INT32_MAX;
     }
     std::vector<TileInfo> ti(S);
-    for (auto& t : ti) { t = TileInfo{}; t.first_pc[0] = t.first_pc[1] = INT32_MAX; }
+    for (auto& t : ti) { t = TileInfo{}; t.first_pc = t.empty_rank = INT32_MAX; }
     HIPCHK(h, hipMemcpyAsync(a.st.ctl, c.data(), S * sizeof(Ctl), hipMemcpyHostToDevice, h->stream));
     HIPCHK(h, hipMemcpyAsync(a.st.tinfo, ti.data(), S * sizeof(TileInfo), hipMemcpyHostToDevice, h->stream));
     a.st.q_lin = q_l_in;
@@ -1720,6 +1782,7 @@ int sweep(ald_handle_t h, int32_t S, const ald_scenario_t* scen, const int32_t* 
     for (int s = 0; s < S; ++s) a.hscen[s].out_off = (int64_t)s * Q;
     HIPCHK(h, hipMemcpyAsync(a.dscen, a.hscen.data(), S * sizeof(Scen), hipMemcpyHostToDevice, h->stream));
     if (Q > 0) {
+        HIPCHK(h, launch_clear(a.st.any, a.any_words, h->stream));
         HIPCHK(h, launch_query_stats(q_l_in, q_l_pred, Q, a.st.ctl, S, h->stream));
         if (status) {
             rc = ensure_hctl(h, &a);
@@ -1848,7 +1911,8 @@ int ald_worker_summary(ald_handle_t h, int32_t* B, int64_t* sum_c, int64_t* sum_
     if (int rc0 = settle(h, false)) return rc0;
     if (!B || !sum_c || !sum_r || !peak) return fail(h, ALD_EINVAL, "null argument");
     // bring every worker's summaries to the current decode iteration first
-    HIPCHK(h, launch_build(h->main->st, h->stream, 2));
+    HIPCHK(h, launch_build(h->main->st, h->stream, 2, BUILT_BASE | BUILT_TABLE | BUILT_TIES, h->main->small));
+    h->main->have = BUILT_BASE | BUILT_TABLE | BUILT_TIES;
     HIPCHK(h, launch_summary(h->main->st, h->W, B, sum_c, sum_r, peak, h->stream));
     HIPCHK(h, hipStreamSynchronize(h->stream));
     h->rebuild_pending = false;

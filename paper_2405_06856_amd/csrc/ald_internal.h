@@ -33,19 +33,21 @@
 
 namespace ald {
 
-constexpr int TOPK = 4;            // feasible candidates kept per query
 constexpr int EVAL_THREADS = 256;  // threads per pair-evaluation block
 constexpr int EVAL_QPT = 4;        // queries per pair-evaluation thread
 constexpr int EVAL_Q = EVAL_THREADS * EVAL_QPT;  // queries per pair-evaluation block
 constexpr int EVAL_WPB_MAX = 64;  // workers per pair-evaluation block at most
 constexpr int STAGE_MAX = 768;     // live requests of a worker the evaluation stages in LDS (fewer than)
 constexpr int SORT_MIN_TILE = 16384;  // one-scenario tiles at least this long are evaluated in l_pred order
+constexpr int SHORT_TILE = 256;    // tiles of at most this many queries take the short evaluation
+constexpr int SHORT_WPB = 64;      // workers per block of it at most
+constexpr int SHORT_STAGE = 256;   // it searches the ends of workers with fewer live requests in LDS
+constexpr int SMALL_SLOTS = 512;   // workers of at most this many request slots are built by one wave
 constexpr int SEL_THREADS = 256;   // queries per selection block
 constexpr int COMMIT_THREADS = 64;  // the arrival-order commit runs as one wave
-constexpr int HOT = 8192;          // most request slots per worker (commit keeps one worker in LDS)
+constexpr int HOT = 8192;          // most request slots per worker (the commit can hold one such worker in LDS)
 constexpr int BUILD_THREADS = 256;
 constexpr int MAX_DIRTY = 64;      // workers changed within one tile before the tile is cut
-constexpr int COMMIT_CACHE_W = 2048;  // workers of a scenario whose scan rows the commit can keep in LDS
 #ifndef ALD_STALE_CUT
 #define ALD_STALE_CUT 24
 #endif
@@ -58,6 +60,15 @@ constexpr int32_t NEG = INT32_MIN;
 constexpr int32_t PME_NONE = -(1 << 30);
 constexpr int LB_MAX = 2048;       // l_pred range of a worker's breakpoint table
 constexpr int LB_SLOTS = 4096;     // workers with fewer live requests have a breakpoint table
+
+// What a worker's summaries hold (State::built, a set of these; 0: stale): the
+// sums, slot summaries and thresholds; the breakpoint table of every worker
+// (else only of those the short evaluation does not search); the near-tie bands.
+constexpr int32_t BUILT_BASE = 1, BUILT_TABLE = 2, BUILT_TIES = 4;
+__host__ __device__ inline bool has_table(int B, int need)
+{
+    return B < LB_SLOTS && B >= ((need & BUILT_TABLE) ? 1 : SHORT_STAGE);
+}
 
 // error codes raised on the device (mirrors ALD_E* in aladdin.h)
 constexpr int32_t DEV_EINVAL = -1;
@@ -73,7 +84,7 @@ struct Scen {
     int32_t nblk;       // worker blocks (ceil(W / wpb))
     int32_t eval_blk0;  // first pair-evaluation block of this scenario
     int32_t sel_blk0;   // first selection block
-    int32_t fin_blk0;   // the scenario's commit block
+    int32_t sel_n;      // selection blocks
     int32_t sel_g;      // waves of a selection block that share one 64-query group (1, 2 or 4)
     int32_t uniform_M;  // every worker has the same capacity: empty workers are interchangeable
     int32_t mono;       // k1, k1q >= 0: the TTFT of a pair grows with l_in (integer thresholds apply)
@@ -81,9 +92,11 @@ struct Scen {
                         // from the coefficients), so near-tie margins have integer forms too
     int32_t use_d;      // the residents' decode history is known: constraint (d) is checked
     int64_t bits_off;   // uint64 words into bits_feas / bits_nt
-    int64_t part_off;   // int4 entries into part (worker block major: part_off + wb * pstride + query)
+    int64_t part_off;   // entries into part (worker block major: part_off + wb * pstride + query;
+                        // two per query in short tiles)
     int64_t pstride;    // queries per tile rounded up to whole evaluation chunks
     int64_t qsum_off;   // QSum entries into qsum
+    int64_t any_off;    // uint64 words into any (one per 64-query group)
     int64_t out_off;    // offset into out_worker
     // The scenario's query i is entry qmap[i] of the call's query arrays (and
     // of out_worker after out_off, and of out_diag), or entry i when qmap is
@@ -137,28 +150,24 @@ __host__ __device__ inline int32_t ctl_status(const Ctl& c)
     return c.start < c.Q ? ALD_EINCOMPLETE : ALD_OK;
 }
 
-// Tile description published by the selection kernel for the commit kernel.
+// What the pair evaluation tells the commit of the tile (reset by the commit).
 struct TileInfo {
-    int32_t start, end, parity, pad;
-    int32_t first_pc[2];  // first query of the tile with a feasible worker (by round parity)
+    int32_t first_pc;  // first query of the tile with a feasible worker (INT32_MAX: none)
+    // Without diagnostics, workers without a request (State::B = 0) of a
+    // scenario with one capacity are evaluated once per block, as they are all
+    // alike: the rank of the first of them (INT32_MAX: every worker has bit
+    // words of its own).  They rank last; every one's bits are that one's.
+    int32_t empty_rank;
+    int32_t pad[2];
 };
 
-// Per-query result of the selection kernel (tile-start state), kept by tile
-// position (the query's offset, or its place in the sorted layout).  With
-// interchangeable empty workers (uniform capacity), empty workers are not listed
-// one by one: `efeas` says whether an empty worker is feasible (all are alike).
+// Per-query result of the selection kernel (tile-start state, diagnostics
+// only), kept by tile offset.
 struct QSum {
-    uint64_t tkey[TOPK];  // best feasible listed workers: rank keys, descending
-    int32_t tw[TOPK];     // their indices (-1 = none)
-    uint64_t ntkey;       // best-ranked worker with a near-tie margin
-    int32_t ntw;          // its index (-1 = none)
+    int32_t nfeas;        // feasible workers
     int32_t ntcnt;        // workers with a near-tie margin
-    int32_t nfeas;        // feasible workers (all kinds)
-    int32_t ncand;        // feasible workers of the listed kind
-    int32_t efeas;        // an empty worker is feasible
     int32_t ex1, w1;      // smallest KV excess (ties: highest index first)
     int32_t ex2, w2;      // second smallest
-    int32_t pad;
 };
 
 // Device mirror of ald_query_diag_t.
@@ -177,15 +186,18 @@ struct State {
     int32_t* cap;
     int32_t* n;
     int32_t* head;
+    int32_t* tn;       // requests the commit appended behind the sorted slots, from slot n on
+                       // (wrapping at the end of the slot range), until the build sorts them in
     int32_t* M;
     int64_t* S1;
     int64_t* S2;
     int32_t* hbs;      // heartbeat stamp of S1/S2
-    int32_t* built;
+    int32_t* built;    // BUILT_* of its summaries
     int32_t* B;
     int64_t* DS;       // 2^gs * sum(c) + gn * sum(r)
     uint64_t* key;     // (2^gs B)^2 + DS^2
     int32_t* peak;     // KV peak without a new query
+    int32_t* peake;    // an end iteration at which it falls (INT32_MAX: no request)
     double* rhs;       // theta * ((T_dec - c3) - c2 * (B + 1))
     int64_t* SC;       // sum(c)
     int64_t* SR;       // sum(r)
@@ -225,7 +237,7 @@ struct State {
     int32_t* e;
     int32_t* s;
     int4* pms;         // {pme, sm, ss, unused}
-    // per worker [NW * LB_MAX] (built workers with B > 0): entry v - 1 = number of
+    // per worker [NW * LB_MAX] (has_table): entry v - 1 = 16 times the number of
     // live requests with remaining length below v, v = 1 .. LB_MAX
     uint16_t* lbt;
     // per scenario [S]
@@ -243,6 +255,8 @@ struct State {
     // tile scratch
     uint64_t* bits_feas;
     uint64_t* bits_nt;
+    uint64_t* any;     // per 64-query group of bit words: queries with a feasible worker (zero between tiles)
+    int32_t* order;    // [NW] per scenario, from wbase on: its workers by Algorithm 1's rank at tile start
     // Sorted tile layout (one-scenario tiles of at least SORT_MIN_TILE queries;
     // null otherwise): the pair evaluation takes each chunk of EVAL_Q queries in
     // order of l_pred, and the bit words and excess keys are kept by that order.
@@ -250,7 +264,9 @@ struct State {
     // inverse (both per tile offset, pstride entries).
     int32_t* qorig;
     int32_t* qpos;
-    ulonglong2* part;  // per (worker block, query): the two smallest KV-excess keys
+    ulonglong2* part;  // per (worker block, query): the two smallest KV-excess keys; in short
+                       // tiles followed by {feasible workers, near-tie workers}
+    int32_t brief;     // short tiles (SHORT_TILE): k_eval_short, and no selection kernel
     QSum* qsum;
     // queries and outputs
     const int32_t* q_lin;
@@ -277,8 +293,9 @@ inline __host__ __device__ int32_t tile_end(int32_t start, int32_t Q, int32_t T,
 hipError_t launch_ingest(const State& st, int32_t W, const int64_t* res_off, const int32_t* lin,
                          const int32_t* lpred, const int32_t* gen, const double* tdec, hipStream_t stream);
 // mode 0: every worker whose summaries are stale; 1: only the workers listed by
-// the last commit; 2: every worker unconditionally
-hipError_t launch_build(const State& st, hipStream_t stream, int mode);
+// the last commit; 2: every worker unconditionally.  need: BUILT_* to build.
+// small: no worker has more than SMALL_SLOTS slots
+hipError_t launch_build(const State& st, hipStream_t stream, int mode, int need, bool small);
 // mode 0: latency checks in fp64; 1: integer thresholds, near-tie margins in
 // fp64; 2: integer thresholds and near-tie sets; 3: as 2, with the workers too
 // large to stage read through their breakpoint tables in global memory (a
@@ -290,14 +307,15 @@ hipError_t launch_eval(const State& st, int32_t blocks, int mode, hipStream_t st
 int eval_blocks_per_cu(int mode, bool ex);
 hipError_t launch_select(const State& st, int32_t blocks, hipStream_t stream);
 // use_d: some scenario checks constraint (d)
-// cache: the variant that keeps the untouched-worker scan's bit rows and rank
-// keys in LDS (scenarios of at most COMMIT_CACHE_W workers)
-hipError_t launch_commit(const State& st, int32_t blocks, bool use_d, bool cache, hipStream_t stream);
+hipError_t launch_commit(const State& st, int32_t blocks, bool use_d, hipStream_t stream);
 hipError_t launch_query_stats(const int32_t* lin, const int32_t* lpred, int32_t Q, Ctl* ctl, int32_t S,
                               hipStream_t stream);
 // gate: -1, or the asynchronous call that must have finished for this one to start
+// any[0, words): the call's group words, cleared
 hipError_t launch_begin(const Ctl& c, const TileInfo& ti, Ctl* ctl, TileInfo* tinfo, int32_t* qbad, int32_t gate,
-                        hipStream_t stream);
+                        uint64_t* any, int64_t words, hipStream_t stream);
+// any[0, words) = 0
+hipError_t launch_clear(uint64_t* any, int64_t words, hipStream_t stream);
 // status = ALD_OK (an asynchronous call with no queries)
 hipError_t launch_status_ok(int32_t* status, hipStream_t stream);
 hipError_t launch_summary(const State& st, int32_t W, int32_t* B, int64_t* sc, int64_t* sr, int64_t* peak,

@@ -3,15 +3,15 @@
 //
 // Per tile of T consecutive queries (one heartbeat segment at most):
 //   k_build   rebuild the breakpoint summaries of workers whose live set moved
-//   k_eval    every (query, worker) pair of the tile against the tile-start
+//   k_eval    (k_eval_short where the tile is short) every (query, worker) pair of the tile against the tile-start
 //             state: KV peak (constraint (e)), decode (b), TTFT (c), near-tie
-//             margins; feasibility / near-tie bits and per-block KV-excess minima
-//   k_select  per query: best feasible workers by Algorithm 1's rank, counts,
-//             the two smallest KV excesses, the best near-tie worker
-//   k_commit  arrival-order commit: one block per scenario walks the tile,
+//             margins; feasibility / near-tie bits, per-block KV-excess minima,
+//             the workers' rank order
+//   k_select  (diagnostics, long tiles) per query: feasible and near-tie counts, the
+//             two smallest KV excesses, the outputs of queries no worker can take
+//   k_commit  arrival-order commit: one wave per scenario walks the tile,
 //             re-evaluating only workers changed earlier in the same tile, and
-//             cuts the tile when the tile-start lists cannot decide exactly;
-//             extra blocks finalize the rejected prefix in parallel
+//             cuts the tile when the tile-start results cannot decide exactly
 //             (ald_commit.h; launched from ald_commit.hip and ald_commit_d.hip).
 #include "ald_device.h"
 
@@ -20,10 +20,140 @@
 namespace ald {
 
 // ---------------------------------------------------------------------------------------------
+// Sort the requests a commit appended behind a worker's slots [head, n) into
+// them, and move the whole to the start of the slot range (whole block): each
+// request's place is counted (a sorted one moves up by the appended ones ending
+// strictly before it; an appended one goes behind every sorted one ending no
+// later and every earlier appended one ending no later).  The worker's summary
+// slots, which are rebuilt afterwards, hold the result in between.
+constexpr int TAIL_LDS = 1024;  // appended requests whose ends are kept in LDS (more are read from memory)
+__device__ void merge_tail(int32_t* e, int32_t* s, int4* tmp, int head, int n, int cap, int m, int32_t* te)
+{
+    constexpr int NT = BUILD_THREADS;
+    const int tid = threadIdx.x;
+    const int L = n - head;
+    auto at = [&](int t) { return n + t > cap ? n + t - (cap + 1) : n + t; };
+    for (int t = tid; t < min(m, TAIL_LDS); t += NT) te[t] = e[at(t)];
+    __syncthreads();
+    auto tail = [&](int t) { return t < TAIL_LDS ? te[t] : e[at(t)]; };
+    for (int k = tid; k < L; k += NT) {
+        const int32_t x = e[head + k];
+        int up = 0;
+        for (int t = 0; t < m; ++t) up += tail(t) < x ? 1 : 0;
+        tmp[k + up].x = x;
+        tmp[k + up].y = s[head + k];
+    }
+    for (int t = tid; t < m; t += NT) {
+        const int32_t x = tail(t);
+        int to = lower_bound_i32(e, head, n, x + 1) - head;
+        for (int j = 0; j < m; ++j) {
+            const int32_t v = tail(j);
+            to += (v < x || (v == x && j < t)) ? 1 : 0;
+        }
+        tmp[to].x = x;
+        tmp[to].y = s[at(t)];
+    }
+    __syncthreads();
+    for (int k = tid; k < L + m; k += NT) {
+        e[k] = tmp[k].x;
+        s[k] = tmp[k].y;
+    }
+    __syncthreads();
+}
+
+// Integer forms of a built worker's latency checks.  Both left sides are rounded
+// fp64 expressions that never decrease as DS + qD (resp. l_in) grows -- each step
+// is an exact conversion, a product with a non-negative constant or a sum,
+// and rounding is monotone -- so each check holds exactly up to a threshold,
+// found by searching with the very expression the pair check evaluates.
+// Queries have qD <= 2^33 and l_in <= 2^24; DS < 2^31.
+struct Sums {
+    int64_t DS, S1, S2;
+    double rhs, dlim;
+};
+constexpr int64_t XMAX = (int64_t)1 << 36;
+constexpr int64_t LMAX = (int64_t)1 << 24;
+
+// An estimate of the largest l with c1 + k1 (S1 + l) + k1q (S2 + l^2) <= t.
+__device__ __forceinline__ double ttft_root(const Scen& sc, const Sums& u, double t)
+{
+    const double c = t - ((sc.c1 + sc.k1 * (double)u.S1) + sc.k1q * (double)u.S2);
+    return 2.0 * c / (sc.k1 + sqrt(fmax(0.0, sc.k1 * sc.k1 + 4.0 * sc.k1q * c)));
+}
+
+// The thresholds of (b) and of (c) with (d) (one whole wave).
+__device__ void build_limits(const State& st, const Scen& sc, int gw, const Sums& u)
+{
+    const double per = ldexp(1.0, sc.gs) / sc.k2;
+    const int64_t x = wave_last_true_near(u.rhs * per, 0, XMAX, [&](int64_t v) { return dec_lhs(sc, v) <= u.rhs; });
+    // (c) and (d) bound the same prefill time
+    const int64_t l = wave_last_true_near(ttft_root(sc, u, fmin(sc.ttft, u.dlim)), 1, LMAX, [&](int64_t v) {
+        const double t = ttft_of(sc, u.S1 + v, u.S2 + v * v);
+        return t <= sc.ttft && t <= u.dlim;
+    });
+    if (lane_id() == 0) {
+        st.dq_max[gw] = x - u.DS;
+        st.lthr[gw] = (int32_t)l;
+    }
+}
+
+// The near-tie bands of (b) (`decode`) or of (c) and (d) (one whole wave).
+// Inside a band of at most 64 values the margin test itself is run once per
+// value (one per lane), giving the exact near-tie set as a bit mask.
+__device__ void build_ties(const State& st, const Scen& sc, int gw, const Sums& u, bool decode, int32_t* err)
+{
+    const bool l0 = lane_id() == 0;
+    if (decode) {
+        const double per = ldexp(1.0, sc.gs) / sc.k2;
+        const double band = tie_band(u.rhs);
+        const double lo = u.rhs - band, hi = u.rhs + band;
+        const int64_t xl = wave_last_true_near(lo * per, 0, XMAX, [&](int64_t v) { return dec_lhs(sc, v) < lo; }) + 1;
+        const int64_t xh = wave_last_true_near(hi * per, 0, XMAX, [&](int64_t v) { return dec_lhs(sc, v) <= hi; });
+        const int64_t width = xh - xl + 1;
+        const uint64_t mask = ballot(lane_id() < width && near_tie(dec_lhs(sc, xl + lane_id()), u.rhs));
+        if (l0) {
+            st.ntd_lo[gw] = xl - u.DS;
+            st.ntd_hi[gw] = xh - u.DS;
+            st.ntd_mask[gw] = width <= 64 ? mask : 0;
+            if (width > 64 && sc.ntint) raise_error(err, DEV_EOVERFLOW);
+        }
+        return;
+    }
+    auto tt = [&](int64_t l) { return ttft_of(sc, u.S1 + l, u.S2 + l * l); };
+    // the TTFT band (empty on a decode worker, whose T_pre is +inf)
+    int64_t ll = 1, lh = 0;
+    if (sc.ttft != INFINITY) {
+        const double band = tie_band(sc.ttft);
+        const double lo = sc.ttft - band, hi = sc.ttft + band;
+        ll = wave_last_true_near(ttft_root(sc, u, lo), 1, LMAX, [&](int64_t v) { return tt(v) < lo; }) + 1;
+        lh = wave_last_true_near(ttft_root(sc, u, hi), 1, LMAX, [&](int64_t v) { return tt(v) <= hi; });
+    }
+    const int64_t width = lh - ll + 1;
+    const uint64_t mask = ballot(lane_id() < width && near_tie(tt(ll + lane_id()), sc.ttft));
+    if (l0) {
+        st.ntt_lo[gw] = (int32_t)ll;
+        st.ntt_hi[gw] = (int32_t)lh;
+        st.ntt_mask[gw] = width <= 64 ? mask : 0;
+        if (width > 64 && sc.ntint) raise_error(err, DEV_EOVERFLOW);
+    }
+    // the band of (d)'s limit (empty without one)
+    int64_t pl = 1, ph = 0;
+    if (u.dlim != INFINITY) {
+        const double band = tie_band(u.dlim);
+        const double lo = u.dlim - band, hi = u.dlim + band;
+        pl = wave_last_true_near(ttft_root(sc, u, lo), 1, LMAX, [&](int64_t v) { return tt(v) < lo; }) + 1;
+        ph = wave_last_true_near(ttft_root(sc, u, hi), 1, LMAX, [&](int64_t v) { return tt(v) <= hi; });
+    }
+    if (l0) {
+        st.ntp_lo[gw] = (int32_t)pl;
+        st.ntp_hi[gw] = (int32_t)ph;
+    }
+}
+
 // Breakpoint summaries of one worker (whole block).  Drops finished requests
 // (e < tau), recomputes ss / pme / sm over the live slots and the worker's
 // aggregates.  Called with every thread of a BUILD_THREADS block.
-__device__ void build_worker(const State& st, const Scen& sc, int gw, int32_t tau, int32_t hb, int32_t* err)
+__device__ void build_worker(const State& st, const Scen& sc, int gw, int32_t tau, int32_t hb, int need, int32_t* err)
 {
     constexpr int NT = BUILD_THREADS;
     __shared__ int64_t red[NT / 64];
@@ -32,8 +162,20 @@ __device__ void build_worker(const State& st, const Scen& sc, int gw, int32_t ta
     int32_t* e = st.e + base;
     int32_t* s = st.s + base;
     int4* pms = st.pms + base;
-    const int n = st.n[gw];
+    __shared__ int32_t hist[LB_MAX];  // (first the appended requests' ends)
+    static_assert(TAIL_LDS <= LB_MAX, "the ends fit");
+    int n = st.n[gw];
     int head = st.head[gw];
+    const int tn = st.tn[gw];
+    if (tn > 0) {
+        merge_tail(e, s, pms, head, n, st.cap[gw], tn, hist);
+        n = n - head + tn;
+        head = 0;
+        if (tid == 0) {
+            st.n[gw] = n;
+            st.tn[gw] = 0;
+        }
+    }
 
     // Constraint (d): bring the worker's slack gain phi up to the current
     // heartbeat.  Each heartbeat since the last update ran one decode iteration
@@ -85,10 +227,12 @@ __device__ void build_worker(const State& st, const Scen& sc, int gw, int32_t ta
     block_scan_excl<NT, true>(le, 0, OpAdd(), &tot_e, red);
 
     int64_t run = soff, lmaxP = INT64_MIN, lmaxPe = INT64_MIN;
+    int32_t peake = INT32_MAX;  // the end at which this thread's largest P falls
     for (int k = k1 - 1; k >= k0; --k) {
         run += s[k];
         pms[k].z = (int32_t)run;
         const int64_t P = run + (int64_t)(n - k) * e[k];
+        peake = P >= lmaxP ? e[k] : peake;
         lmaxP = P > lmaxP ? P : lmaxP;
         const int64_t Pe = P + e[k];
         lmaxPe = Pe > lmaxPe ? Pe : lmaxPe;
@@ -96,6 +240,11 @@ __device__ void build_worker(const State& st, const Scen& sc, int gw, int32_t ta
     int64_t totP, totPe;
     const int64_t smoff = block_scan_excl<NT, true>(lmaxP, INT64_MIN, OpMax(), &totP, red);
     const int64_t pmoff = block_scan_excl<NT, false>(lmaxPe, INT64_MIN, OpMax(), &totPe, red);
+    // the earliest end at which the worker's peak falls
+    __shared__ int32_t first_peak;
+    if (tid == 0) first_peak = INT32_MAX;
+    __syncthreads();
+    if (lmaxP == totP && k0 < k1) atomicMin(&first_peak, peake);
 
     int64_t runmax = smoff;
     for (int k = k1 - 1; k >= k0; --k) {
@@ -146,6 +295,7 @@ __device__ void build_worker(const State& st, const Scen& sc, int gw, int32_t ta
     }
     if (tid == 0) st.dlim[gw] = dl;
 
+    __syncthreads();  // first_peak
     const int64_t SC = tot_s + (int64_t)B * tau;
     const int64_t SR = tot_e - (int64_t)B * tau;
     const int64_t DS = (SC << sc.gs) + (int64_t)sc.gn * SR;
@@ -162,15 +312,15 @@ __device__ void build_worker(const State& st, const Scen& sc, int gw, int32_t ta
         st.DS[gw] = DS;
         st.key[gw] = key;
         st.peak[gw] = B > 0 ? (int32_t)totP : 0;
+        st.peake[gw] = B > 0 ? first_peak : INT32_MAX;
         st.rhs[gw] = rhs;
     }
-    // Breakpoint table (workers with 0 < B < LB_SLOTS): a histogram of the
+    // Breakpoint table (has_table): a histogram of the
     // remaining lengths r = e - tau of the live requests (those below LB_MAX),
     // then an exclusive scan, so that entry v - 1 = the byte offset, from the
     // first live slot's summaries, of the first live slot with r >= v (16
     // bytes per slot before it).
-    if (B > 0 && B < LB_SLOTS) {
-        __shared__ int32_t hist[LB_MAX];
+    if (has_table(B, need)) {
         for (int v = tid; v < LB_MAX; v += NT) hist[v] = 0;
         __syncthreads();
         for (int k = head + tid; k < n; k += NT) {
@@ -193,73 +343,13 @@ __device__ void build_worker(const State& st, const Scen& sc, int gw, int32_t ta
             out[tid * CHV + j] = (uint16_t)(run * (int32_t)sizeof(int4));  // entry v - 1, v = tid * CHV + j + 1
         }
     }
-    // Integer forms of the latency checks.  Both left sides are rounded fp64
-    // expressions that never decrease as DS + qD (resp. l_in) grows -- each step
-    // is an exact conversion, a product with a non-negative constant or a sum,
-    // and rounding is monotone -- so each check holds exactly up to a threshold,
-    // found by searching with the very expression the pair check evaluates.
-    // Queries have qD <= 2^33 and l_in <= 2^24; DS < 2^31.
-    constexpr int64_t XMAX = (int64_t)1 << 36;
-    constexpr int64_t LMAX = (int64_t)1 << 24;
+    const bool cur = st.hbs[gw] == hb;
+    const Sums u{DS, cur ? st.S1[gw] : 0, cur ? st.S2[gw] : 0, rhs, dl};
     const int wv = wave_id();
-    const bool l0 = lane_id() == 0;
-    // Inside a band of at most 64 values the margin test itself is run once per
-    // value (one per lane), giving the exact near-tie set as a bit mask.
     if (wv == 0) {
-        const int64_t x = wave_last_true(0, XMAX, [&](int64_t v) { return dec_lhs(sc, v) <= rhs; });
-        if (l0) st.dq_max[gw] = x - DS;
-    } else if (wv == 1) {
-        const double band = tie_band(rhs);
-        const double lo = rhs - band, hi = rhs + band;
-        const int64_t xl = wave_last_true(0, XMAX, [&](int64_t v) { return dec_lhs(sc, v) < lo; }) + 1;
-        const int64_t xh = wave_last_true(0, XMAX, [&](int64_t v) { return dec_lhs(sc, v) <= hi; });
-        const int64_t width = xh - xl + 1;
-        const uint64_t mask = ballot(lane_id() < width && near_tie(dec_lhs(sc, xl + lane_id()), rhs));
-        if (l0) {
-            st.ntd_lo[gw] = xl - DS;
-            st.ntd_hi[gw] = xh - DS;
-            st.ntd_mask[gw] = width <= 64 ? mask : 0;
-            if (width > 64 && sc.ntint) raise_error(err, DEV_EOVERFLOW);
-        }
-    } else if (wv <= 3) {
-        const bool cur = st.hbs[gw] == hb;
-        const int64_t S1 = cur ? st.S1[gw] : 0;
-        const int64_t S2 = cur ? st.S2[gw] : 0;
-        auto tt = [&](int64_t l) { return ttft_of(sc, S1 + l, S2 + l * l); };
-        if (wv == 2) {
-            // (c) and (d) bound the same prefill time
-            const int64_t l = wave_last_true(1, LMAX, [&](int64_t v) { const double t = tt(v); return t <= sc.ttft && t <= dl; });
-            if (l0) st.lthr[gw] = (int32_t)l;
-        } else {
-            // the TTFT band (empty on a decode worker, whose T_pre is +inf)
-            int64_t ll = 1, lh = 0;
-            if (sc.ttft != INFINITY) {
-                const double band = tie_band(sc.ttft);
-                const double lo = sc.ttft - band, hi = sc.ttft + band;
-                ll = wave_last_true(1, LMAX, [&](int64_t v) { return tt(v) < lo; }) + 1;
-                lh = wave_last_true(1, LMAX, [&](int64_t v) { return tt(v) <= hi; });
-            }
-            const int64_t width = lh - ll + 1;
-            const uint64_t mask = ballot(lane_id() < width && near_tie(tt(ll + lane_id()), sc.ttft));
-            if (l0) {
-                st.ntt_lo[gw] = (int32_t)ll;
-                st.ntt_hi[gw] = (int32_t)lh;
-                st.ntt_mask[gw] = width <= 64 ? mask : 0;
-                if (width > 64 && sc.ntint) raise_error(err, DEV_EOVERFLOW);
-            }
-            // the band of (d)'s limit (empty without one)
-            int64_t pl = 1, ph = 0;
-            if (dl != INFINITY) {
-                const double pband = tie_band(dl);
-                const double plo = dl - pband, phi_ = dl + pband;
-                pl = wave_last_true(1, LMAX, [&](int64_t v) { return tt(v) < plo; }) + 1;
-                ph = wave_last_true(1, LMAX, [&](int64_t v) { return tt(v) <= phi_; });
-            }
-            if (l0) {
-                st.ntp_lo[gw] = (int32_t)pl;
-                st.ntp_hi[gw] = (int32_t)ph;
-            }
-        }
+        build_limits(st, sc, gw, u);
+    } else if (wv <= 2 && (need & BUILT_TIES)) {
+        build_ties(st, sc, gw, u, wv == 1, err);
     }
     __syncthreads();
 }
@@ -360,6 +450,7 @@ __global__ __launch_bounds__(BUILD_THREADS) void k_ingest(State st, const int64_
     if (tid == 0) {
         st.n[gw] = R;
         st.head[gw] = 0;
+        st.tn[gw] = 0;
         st.built[gw] = 0;
         st.S1[gw] = 0;
         st.S2[gw] = 0;
@@ -369,44 +460,342 @@ __global__ __launch_bounds__(BUILD_THREADS) void k_ingest(State st, const int64_
 }
 
 // ---------------------------------------------------------------------------------------------
-// One worker's rebuild decision and build (all threads of the block).
-__device__ __forceinline__ void build_one(const State& st, int mode, int gw, int s)
+// Does worker gw of scenario s have to be built now?
+__device__ __forceinline__ bool must_build(const State& st, int mode, int need, int gw, int s)
 {
     const Ctl* c = st.ctl + s;
-    if (mode != 2 && c->call != st.call) return;  // another call's control block
+    if (mode == 2) return true;
+    if (c->call != st.call) return false;  // another call's control block
     if (mode == 0) {
-        if (c->err || c->start >= c->Q) return;
-        if (st.built[gw]) {
-            if (!c->rebuild) return;
+        if (c->err || c->start >= c->Q) return false;
+        const int32_t built = st.built[gw];
+        if ((built & need) == need) {
+            if (!c->rebuild) return false;
             // A worker that held no live request at its last build and has taken
             // none since (a placement clears `built`), with no prefill sum, has
             // the same summaries and thresholds at any tau: only the slack clock
             // of constraint (d) moves on (its gain is zero without a batch).
             if (st.B[gw] == 0 && st.S1[gw] == 0) {
-                if (threadIdx.x == 0 && st.scen[s].use_d) st.phi_hb[gw] = c->hb_index;
-                return;
+                if (lane_id() == 0 && st.scen[s].use_d) st.phi_hb[gw] = c->hb_index;
+                return false;
             }
         }
     }
-    const Scen sc = st.scen[s];
-    build_worker(st, sc, gw, c->tau, c->hb_index, &st.ctl[s].err);
-    if (threadIdx.x == 0) st.built[gw] = 1;
+    return true;
 }
 
 // mode 1: the workers the last commit round listed; modes 0 and 2: every
 // worker (one block each).
-__global__ __launch_bounds__(BUILD_THREADS) void k_build(State st, int mode)
+__global__ __launch_bounds__(BUILD_THREADS) void k_build(State st, int mode, int need)
 {
+    int s, gw;
     if (mode == 1) {
-        const int s = blockIdx.x / MAX_DIRTY;
+        s = blockIdx.x / MAX_DIRTY;
         const int j = blockIdx.x % MAX_DIRTY;
         if (s >= st.S || j >= st.dcount[s]) return;
-        const int gw = st.dlist[s * MAX_DIRTY + j];
-        if (st.built[gw]) return;
-        build_one(st, mode, gw, s);
-        return;
+        gw = st.dlist[s * MAX_DIRTY + j];
+        if ((st.built[gw] & need) == need) return;
+    } else {
+        gw = blockIdx.x;
+        s = find_scen_by_worker(st, gw);
     }
-    build_one(st, mode, blockIdx.x, find_scen_by_worker(st, blockIdx.x));
+    if (!must_build(st, mode, need, gw, s)) return;
+    const Scen sc = st.scen[s];
+    build_worker(st, sc, gw, st.ctl[s].tau, st.ctl[s].hb_index, need, &st.ctl[s].err);
+    if (threadIdx.x == 0) st.built[gw] = need;
+}
+
+// The same build by one wave per worker, for workers of at most SMALL_SLOTS
+// slots: a block barrier per scan costs such a worker more than the scan.  Lane l
+// holds slots 64 c + l in registers; scans are cross-lane, with a carry over
+// the chunks c, and everything is 32-bit (a demand is below 2^31, a sum of
+// s = c - tau within 2^30 + 2^27); only the sum of the ends is not.
+constexpr int SMALL_CH = SMALL_SLOTS / 64;
+constexpr int SMALL_WAVES = 4;  // workers per block
+
+struct SmallLDS {
+    union {
+        struct {
+            int32_t e[SMALL_SLOTS], s[SMALL_SLOTS];
+        };
+        uint16_t mark[LB_MAX];
+    };
+};
+
+__device__ void build_small(const State& st, const Scen& sc, int gw, int32_t tau, int32_t hb, int need, int32_t* err,
+                            SmallLDS& L)
+{
+    const int lane = lane_id();
+    const int64_t base = st.slot_base[gw];
+    int n = st.n[gw], head = st.head[gw];
+    const int tn = st.tn[gw];
+    int32_t e[SMALL_CH], s[SMALL_CH];
+    {
+        const int N = n - head;
+#pragma unroll
+        for (int c = 0; c < SMALL_CH; ++c) {
+            const int k = c * 64 + lane;
+            const bool in = k < N;
+            e[c] = in ? st.e[base + head + k] : 0;
+            s[c] = in ? st.s[base + head + k] : 0;
+        }
+        if (tn > 0) {
+            // sort the appended requests in: every request's place is counted (see
+            // merge_tail), in LDS, and the whole moves to the start of the slot range
+            const int cap = st.cap[gw];
+            int32_t up[SMALL_CH];
+#pragma unroll
+            for (int c = 0; c < SMALL_CH; ++c) up[c] = 0;
+            for (int t0 = 0; t0 < tn; t0 += 64) {
+                auto at = [&](int t) { return n + t > cap ? n + t - (cap + 1) : n + t; };
+                const int mt = min(64, tn - t0);
+                const int p = at(t0 + min(lane, mt - 1));
+                const int32_t x = st.e[base + p], y = st.s[base + p];
+                int to = 0;
+                for (int j = 0; j < tn; j += 64) {  // against the other appended requests
+                    const int mj = min(64, tn - j);
+                    const int32_t v = j == t0 ? x : st.e[base + at(j + min(lane, mj - 1))];
+                    for (int q = 0; q < mj; ++q) {
+                        const int32_t xq = rdlane(v, q);
+                        to += (xq < x || (xq == x && j + q < t0 + lane)) ? 1 : 0;
+                    }
+                }
+                for (int q = 0; q < mt; ++q) {  // against the sorted ones
+                    const int32_t xq = rdlane(x, q);
+                    int above = 0;
+#pragma unroll
+                    for (int c = 0; c < SMALL_CH; ++c) {
+                        if (c * 64 >= N) break;
+                        const uint64_t m = ballot(c * 64 + lane < N) & ballot(e[c] > xq);
+                        up[c] += __builtin_amdgcn_inverse_ballot_w64(m) ? 1 : 0;
+                        above += __popcll(m);
+                    }
+                    to += lane == q ? N - above : 0;
+                }
+                if (lane < mt) {
+                    L.e[to] = x;
+                    L.s[to] = y;
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < SMALL_CH; ++c) {
+                const int k = c * 64 + lane;
+                if (k < N) {
+                    L.e[k + up[c]] = e[c];
+                    L.s[k + up[c]] = s[c];
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+            n = N + tn;
+            head = 0;
+#pragma unroll
+            for (int c = 0; c < SMALL_CH; ++c) {
+                const int k = c * 64 + lane;
+                const bool in = k < n;
+                e[c] = in ? L.e[min(k, SMALL_SLOTS - 1)] : 0;
+                s[c] = in ? L.s[min(k, SMALL_SLOTS - 1)] : 0;
+                if (in) {
+                    st.e[base + k] = e[c];
+                    st.s[base + k] = s[c];
+                }
+            }
+            if (lane == 0) {
+                st.n[gw] = n;
+                st.tn[gw] = 0;
+            }
+        }
+    }
+    const int N = n - head;
+    // Constraint (d): the worker's slack gain up to the current heartbeat (see
+    // build_worker)
+    double phi = 0.0;
+    if (sc.use_d) {
+        phi = st.phi[gw];
+        const int pending = hb - st.phi_hb[gw];
+        if (pending < 0) {
+            if (lane == 0) raise_error(err, DEV_EINVAL);
+        } else {
+            for (int p = 0; p < pending; ++p) {
+                const int32_t tk = tau - pending + p;
+                int cnt = 0;
+                int32_t part = 0;
+#pragma unroll
+                for (int c = 0; c < SMALL_CH; ++c) {
+                    const bool in = c * 64 + lane < N && e[c] >= tk;
+                    cnt += __popcll(ballot(in));
+                    part += in ? s[c] : 0;
+                }
+                if (cnt == 0) break;  // the live set only shrinks: no later iteration runs a batch
+                const int64_t ctx = (int64_t)wave_sum32(part) + (int64_t)cnt * tk;  // sum of the contexts c = s + tau
+                const double t_iter = (sc.c3 + sc.c2 * (double)cnt) + sc.k2 * (double)ctx;
+                phi = phi + (sc.tdec - t_iter);
+            }
+            if (lane == 0) {
+                st.phi[gw] = phi;
+                st.phi_hb[gw] = hb;
+            }
+        }
+    }
+    // finished requests form a prefix of the live range (sorted by e)
+    int fin = 0;
+#pragma unroll
+    for (int c = 0; c < SMALL_CH; ++c) fin += __popcll(ballot(c * 64 + lane < N && e[c] < tau));
+    const int B = N - fin;
+    head += fin;
+    // from the last slot down: sums of s, the demands P at the end points, their
+    // running maximum
+    int32_t P[SMALL_CH], ss[SMALL_CH], sm[SMALL_CH];
+    int32_t sum = 0, top = NEG, at = INT32_MAX;
+    int64_t se = 0;
+#pragma unroll
+    for (int c = SMALL_CH - 1; c >= 0; --c) {
+        P[c] = NEG;
+        ss[c] = sm[c] = 0;
+        if (c * 64 >= N) continue;
+        const int k = c * 64 + lane;
+        const bool in = k >= fin && k < N;
+        const int32_t sv = in ? s[c] : 0;
+        se += in ? e[c] : 0;
+        // (an inclusive scan from lane 0 up; the suffix is what it leaves)
+        const int32_t inc = wave_incl_scan(sv, 0, Add32());
+        const int32_t all = rdlane(inc, 63);
+        ss[c] = sum + all - inc + sv;
+        sum += all;
+        // (wrap-around arithmetic: the demand itself is below 2^31)
+        P[c] = in ? (int32_t)((uint32_t)ss[c] + (uint32_t)(N - k) * (uint32_t)e[c]) : NEG;
+        const int32_t chunk = wave_max32(P[c]);
+        sm[c] = max(wave_suffix_max(P[c]), top);
+        if (chunk >= top && chunk != NEG) at = rdlane(e[c], __builtin_ctzll(ballot(P[c] == chunk)));  // the earliest end
+        top = max(top, chunk);
+    }
+    int32_t pm = NEG;
+#pragma unroll
+    for (int c = 0; c < SMALL_CH; ++c) {
+        if (c * 64 >= N) break;
+        const int k = c * 64 + lane;
+        const bool in = k >= fin && k < N;
+        const int32_t Pe = in ? P[c] + e[c] : NEG;
+        const int32_t inc = wave_incl_scan(Pe, NEG, Max32());
+        const int32_t below = __shfl_up(inc, 1, 64);  // (every lane takes part)
+        const int32_t before = max(pm, lane == 0 ? NEG : below);
+        pm = max(pm, rdlane(inc, 63));
+        if (in) st.pms[base + head - fin + k] = make_int4(before == NEG ? PME_NONE : before, sm[c], ss[c], N - k);
+    }
+    double dl = INFINITY;
+    if (sc.use_d) {  // constraint (d)'s limit (see build_worker), 64 log entries at a time
+        int32_t* lge = st.lge + base;
+        int32_t* lgw = st.lgw + base;
+        double* lgs = st.lgs + base;
+        const int L0 = st.lgn[gw];
+        int wpos = 0;
+        double mn = INFINITY;
+        for (int c0 = 0; c0 < L0; c0 += 64) {
+            const int k = c0 + lane;
+            const bool in = k < L0;
+            const int32_t ek = in ? lge[k] : 0, wk = in ? lgw[k] : 0;
+            const double sk = in ? lgs[k] : 0.0;
+            const bool keep = in && ek >= tau;
+            if (keep && wk < hb) mn = fmin(mn, sk);
+            const uint64_t m = ballot(keep);
+            if (keep) {  // (kept entries only move down, to places already read)
+                const int to = wpos + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+                lge[to] = ek;
+                lgw[to] = wk;
+                lgs[to] = sk;
+            }
+            wpos += __popcll(m);
+        }
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) mn = fmin(mn, __shfl_xor(mn, d, 64));
+        if (mn != INFINITY) dl = sc.theta * (mn + phi);
+        if (lane == 0) st.lgn[gw] = wpos;
+    }
+    const int64_t SC = (int64_t)sum + (int64_t)B * tau;
+    const int64_t SR = wave_sum64(se) - (int64_t)B * tau;
+    const int64_t DS = (SC << sc.gs) + (int64_t)sc.gn * SR;
+    const double rhs = sc.theta * ((sc.tdec - sc.c3) - sc.c2 * (double)(B + 1));
+    if (lane == 0) {
+        st.pms[base + n] = make_int4(pm == NEG ? PME_NONE : pm, NEG, 0, 0);
+        const int64_t X = (int64_t)B << sc.gs;
+        if (DS >= ((int64_t)1 << 31) || X >= ((int64_t)1 << 31) || DS < 0) raise_error(err, DEV_EOVERFLOW);
+        st.head[gw] = head;
+        st.B[gw] = B;
+        st.SC[gw] = SC;
+        st.SR[gw] = SR;
+        st.DS[gw] = DS;
+        st.key[gw] = (uint64_t)(X * X) + (uint64_t)(DS * DS);
+        st.peak[gw] = B > 0 ? top : 0;
+        st.peake[gw] = B > 0 ? at : INT32_MAX;
+        st.rhs[gw] = rhs;
+        st.dlim[gw] = dl;
+    }
+    if (has_table(B, need)) {
+        // breakpoint table (see build_worker): the requests are sorted, so the last
+        // one of each remaining length r marks entry r with the number ending no
+        // later, and a running maximum fills the entries between
+        for (int v = lane; v < LB_MAX / 8; v += 64) reinterpret_cast<uint4*>(L.mark)[v] = make_uint4(0, 0, 0, 0);
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int c = 0; c < SMALL_CH; ++c) {
+            if (c * 64 >= N) break;
+            const int k = c * 64 + lane;
+            const int32_t ahead = c + 1 < SMALL_CH ? rdlane(e[c + 1 < SMALL_CH ? c + 1 : c], 0) : 0;
+            const int32_t down = __shfl_down(e[c], 1, 64);
+            const int32_t next = lane == 63 ? ahead : down;
+            const int32_t r = e[c] - tau;
+            if (k >= fin && k < N && r < LB_MAX && (k == N - 1 || next != e[c])) L.mark[r] = (uint16_t)(k - fin + 1);
+        }
+        __builtin_amdgcn_wave_barrier();
+        int32_t run = 0;
+        uint4* out = reinterpret_cast<uint4*>(st.lbt + (int64_t)gw * LB_MAX);
+#pragma unroll
+        for (int q = 0; q < LB_MAX / 512; ++q) {
+            const uint4 v = reinterpret_cast<const uint4*>(L.mark)[q * 64 + lane];
+            int32_t m[8] = {(int32_t)(v.x & 0xffff), (int32_t)(v.x >> 16), (int32_t)(v.y & 0xffff), (int32_t)(v.y >> 16),
+                            (int32_t)(v.z & 0xffff), (int32_t)(v.z >> 16), (int32_t)(v.w & 0xffff), (int32_t)(v.w >> 16)};
+#pragma unroll
+            for (int u = 1; u < 8; ++u) m[u] = max(m[u], m[u - 1]);
+            const int32_t inc = wave_incl_scan(m[7], 0, Max32());
+            const int32_t prev = __shfl_up(inc, 1, 64);
+            const int32_t carry = max(run, lane == 0 ? 0 : prev);
+            run = max(run, rdlane(inc, 63));
+            uint32_t o[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)  // byte offsets of the slots' summaries
+                o[u] = (uint32_t)(max(m[2 * u], carry) * (int32_t)sizeof(int4)) |
+                       ((uint32_t)(max(m[2 * u + 1], carry) * (int32_t)sizeof(int4)) << 16);
+            out[q * 64 + lane] = make_uint4(o[0], o[1], o[2], o[3]);
+        }
+    }
+    const bool cur = st.hbs[gw] == hb;
+    const Sums u{DS, cur ? st.S1[gw] : 0, cur ? st.S2[gw] : 0, rhs, dl};
+    build_limits(st, sc, gw, u);
+    if (need & BUILT_TIES) {
+        build_ties(st, sc, gw, u, true, err);
+        build_ties(st, sc, gw, u, false, err);
+    }
+}
+
+__global__ __launch_bounds__(64 * SMALL_WAVES) void k_build_small(State st, int mode, int need)
+{
+    __shared__ SmallLDS L[SMALL_WAVES];
+    const int id = blockIdx.x * SMALL_WAVES + __builtin_amdgcn_readfirstlane(wave_id());
+    int s, gw;
+    if (mode == 1) {
+        s = id / MAX_DIRTY;
+        const int j = id % MAX_DIRTY;
+        if (s >= st.S || j >= st.dcount[s]) return;
+        gw = st.dlist[s * MAX_DIRTY + j];
+        if ((st.built[gw] & need) == need) return;
+    } else {
+        gw = id;
+        if (gw >= st.NW) return;
+        s = find_scen_by_worker(st, gw);
+    }
+    if (!must_build(st, mode, need, gw, s)) return;
+    build_small(st, st.scen[s], gw, st.ctl[s].tau, st.ctl[s].hb_index, need, &st.ctl[s].err,
+                L[__builtin_amdgcn_readfirstlane(wave_id())]);
+    if (lane_id() == 0) st.built[gw] = need;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -457,24 +846,6 @@ __device__ __forceinline__ int64_t block_all(int64_t v, int64_t ident, Op op, in
     return r;
 }
 
-// Two smallest KV excesses of a query as packed keys: excess (offset to
-// unsigned) in the high word, the complement of the worker index in the low
-// word -- smaller key = smaller excess, then higher index (the order the
-// commit's tie rule expects).  ~0 marks an empty entry.
-__device__ __forceinline__ uint64_t ex_key(int32_t ex, int32_t w)
-{
-    return ((uint64_t)((uint32_t)ex ^ 0x80000000u) << 32) | (uint32_t)~(uint32_t)w;
-}
-__device__ __forceinline__ void ex_unpack(uint64_t k, int32_t& ex, int32_t& w)
-{
-    ex = k == ~0ull ? INT32_MAX : (int32_t)((uint32_t)(k >> 32) ^ 0x80000000u);
-    w = k == ~0ull ? -1 : (int32_t)~(uint32_t)k;
-}
-
-// LLVM's writelane intrinsic (v_writelane_b32): the value of lane `lane` of
-// `old` replaced by the wave-uniform `v`.  Through the intrinsic the compiler
-// sees the instruction and inserts whatever wait states its operands need.
-__device__ int ald_writelane(int v, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
 // v_mul_u32_u24: the product of the low 24 bits of each operand (full rate)
 __device__ uint32_t ald_mul_u24(uint32_t a, uint32_t b) __asm("llvm.amdgcn.mul.u24");
 
@@ -557,10 +928,11 @@ __device__ __forceinline__ void stage_put(uint16_t* LBs, int4* Ss, const Prefetc
 }
 
 // First worker at or after j (block-local index) that is evaluated from LDS.
-__device__ __forceinline__ int next_staged(const WInfo* Wi, int nw, bool use_lb, int j)
+// skip: workers that share another's bit words.
+__device__ __forceinline__ int next_staged(const WInfo* Wi, int nw, bool use_lb, uint64_t skip, int j)
 {
     if (!use_lb) return nw;
-    while (j < nw && Wi[j].n - Wi[j].head >= STAGE_MAX) ++j;
+    while (j < nw && (Wi[j].n - Wi[j].head >= STAGE_MAX || ((skip >> j) & 1))) ++j;
     return j;
 }
 
@@ -582,8 +954,8 @@ __device__ __forceinline__ void eval_worker(const State& st, const Scen& sc, con
                                             const bool (&act)[EVAL_QPT], const uint64_t (&am)[EVAL_QPT],
                                             const int32_t (&qd)[EVAL_QPT], int32_t (&e1)[EVAL_QPT],
                                             int32_t (&w1)[EVAL_QPT], int32_t (&e2)[EVAL_QPT],
-                                            int32_t (&w2)[EVAL_QPT], const uint16_t* LBs, const int4* Ss,
-                                            uint64_t* bdst)
+                                            int32_t (&w2)[EVAL_QPT], uint64_t (&anyb)[EVAL_QPT],
+                                            const uint16_t* LBs, const int4* Ss, uint64_t* bdst)
 {
     constexpr bool MONO = MODE >= 1;
     const int lane = lane_id();
@@ -650,6 +1022,7 @@ __device__ __forceinline__ void eval_worker(const State& st, const Scen& sc, con
             // one ballot per compare: each compare's lane mask is its ballot
             const uint64_t bf = am[m] & ballot(peak[m] <= M) & ballot(bok) & ballot(lin[m] <= lthr);
             bits = put_lane(bits, bf, m);
+            anyb[EX ? 0 : m] |= bf;
             if (EX) keep_two<STAGED>(peak[m] - M, w, e1[m], w1[m], e2[m], w2[m]);
         }
         // near-tie words (lanes EVAL_QPT .. 2 EVAL_QPT - 1) stay zero here: near_tie_words fills
@@ -661,6 +1034,7 @@ __device__ __forceinline__ void eval_worker(const State& st, const Scen& sc, con
             const uint64_t bf = ballot(act[m] && peak[m] <= wi.M && Lt.dec_ok && Lt.ttft_ok);
             const uint64_t bn = ballot(act[m] && Lt.nt);
             bits = put_lane(bits, bf, m);
+            anyb[EX ? 0 : m] |= bf;
             bits = put_lane(bits, bn, m + EVAL_QPT);
             if (EX) keep_two<STAGED>(peak[m] - wi.M, w, e1[m], w1[m], e2[m], w2[m]);
         }
@@ -779,6 +1153,28 @@ __device__ __forceinline__ void sort_chunk(const State& st, const Scen& sc, int 
     __syncthreads();  // the scratch is the staging area of the evaluation
 }
 
+// Write the block's workers (those of this chunk's or group's share) into the
+// rank order, and (empties) the place of the first one without a request.
+// One wave; nw <= 64.
+__device__ __forceinline__ void publish_ranks(const State& st, const Scen& sc, int s, int nw, int wbeg, int share,
+                                              int mine, const int32_t* rk, const uint64_t* wkey, bool empties)
+{
+    const int j = lane_id();
+    const bool in = j < nw && j % share == mine;
+    if (in) st.order[sc.wbase + rk[j]] = wbeg + j;
+    if (empties && sc.uniform_M) {
+        const uint64_t m = ballot(in && wkey[min(j, nw - 1)] == 0);
+        if (m != 0 && j == __builtin_ctzll(m)) atomicMin(&st.tinfo[s].empty_rank, rk[j]);
+    }
+}
+
+// How many of the wave's keys (key kk of worker k, where k < W) rank before
+// worker j of key kj: larger first, the lower index among equal ones.
+__device__ __forceinline__ int count_before(uint64_t kk, int k, int W, uint64_t kj, int j)
+{
+    return __popcll(ballot(k < W) & (ballot(kk > kj) | (ballot(kk == kj) & ballot(k < j))));
+}
+
 // Pair evaluation: block = (scenario, worker block, chunk of EVAL_Q queries).
 // Thread t holds queries t, t + 256, t + 512, t + 768 of the chunk.  For each
 // worker of the block, its summaries and breakpoint table (built with the
@@ -790,7 +1186,8 @@ __device__ __forceinline__ void sort_chunk(const State& st, const Scen& sc, int 
 // latency checks are taken (launch_eval); EX: the two smallest KV excesses are
 // tracked (diagnostics); TAB: unstaged workers are read through their tables.
 template <int MODE, bool EX, bool TAB = false>
-__global__ __launch_bounds__(EVAL_THREADS) __attribute__((amdgpu_waves_per_eu(4))) void k_eval(State st)
+__global__ __launch_bounds__(EVAL_THREADS) __attribute__((amdgpu_waves_per_eu((MODE == 2 && !TAB) ? 5 : 4))) void
+k_eval(State st)
 {
     constexpr int NT = EVAL_THREADS;
     constexpr int QPT = EVAL_QPT;
@@ -798,6 +1195,9 @@ __global__ __launch_bounds__(EVAL_THREADS) __attribute__((amdgpu_waves_per_eu(4)
     __shared__ uint16_t LBs[LB_MAX];               // the worker's breakpoint table
     __shared__ int4 Ss[PF_N * NT];                 // pms of live slot k, k = 0..B
     __shared__ WInfo Wi[EVAL_WPB_MAX];
+    __shared__ int32_t rk[EVAL_WPB_MAX];           // the workers' ranks
+    __shared__ uint64_t wkey[EVAL_WPB_MAX];        // and rank keys
+    __shared__ uint16_t chunk_at[EVAL_Q];          // chunk offset of the query at each position
     __shared__ int64_t red[NT / 64];
     static_assert(sizeof(Ss) >= 10 * 1024, "the sort's scratch");
 
@@ -827,9 +1227,6 @@ __global__ __launch_bounds__(EVAL_THREADS) __attribute__((amdgpu_waves_per_eu(4)
     const int tid = threadIdx.x;
     const int lane = lane_id();
 
-    // Thread tid evaluates chunk positions m * NT + tid: the chunk's queries in
-    // arrival order, or (sorted layout) in order of l_pred.  o[m] = the chunk
-    // offset of the query at position m * NT + tid.
     // Thread tid evaluates chunk positions m * NT + tid: the queries in
     // arrival order, or (sorted layout) in order of l_pred
     int o[QPT];  // chunk offset of the query at position m * NT + tid
@@ -837,6 +1234,9 @@ __global__ __launch_bounds__(EVAL_THREADS) __attribute__((amdgpu_waves_per_eu(4)
     for (int m = 0; m < QPT; ++m) o[m] = m * NT + tid;
     if (st.qorig != nullptr)
         sort_chunk<QPT>(st, sc, start, q0, min(EVAL_Q, end - q0), wb == 0, o, reinterpret_cast<uint16_t*>(Ss), red);
+    // (kept in LDS for the end: registers held over the loop cost a wave per SIMD)
+#pragma unroll
+    for (int m = 0; m < QPT; ++m) chunk_at[m * NT + tid] = (uint16_t)o[m];
     int32_t lin[QPT], lp[QPT];
     bool act[QPT];
     int32_t e1[QPT], w1[QPT], e2[QPT], w2[QPT];  // two smallest KV excesses per query
@@ -845,7 +1245,7 @@ __global__ __launch_bounds__(EVAL_THREADS) __attribute__((amdgpu_waves_per_eu(4)
     for (int m = 0; m < QPT; ++m) {
         act[m] = q0 + m * NT + tid < end;
         lin[m] = act[m] ? st.q_lin[q_at(sc, q0 + o[m])] : 1;
-        lp[m] = act[m] ? st.q_lpred[q_at(sc, q0 + o[m])] : 1;
+        lp[m] = act[m] ? max(st.q_lpred[q_at(sc, q0 + o[m])], 1) : 1;  // (an invalid length fails the call)
         e1[m] = e2[m] = INT32_MAX;
         w1[m] = w2[m] = -1;
         const int64_t qD = ((int64_t)lin[m] << sc.gs) + (int64_t)sc.gn * lp[m];
@@ -909,8 +1309,33 @@ __global__ __launch_bounds__(EVAL_THREADS) __attribute__((amdgpu_waves_per_eu(4)
         x.nt_any = MODE == 0 || (qr.qdmax >= x.ntd_lo && qr.qdmin <= x.ntd_hi) ||
                    (qr.lnmax >= x.ntt_lo && qr.lnmin <= x.ntt_hi) || (qr.lnmax >= x.ntp_lo && qr.lnmin <= x.ntp_hi);
         Wi[tid] = x;
+        rk[tid] = 0;
+        wkey[tid] = st.key[gw];
     }
     __syncthreads();
+
+    // Algorithm 1's rank of the block's workers at tile start, for the commit: a
+    // worker's place is the number of workers that rank before it.  The chunks
+    // of the tile share the block's workers out among them, so that a tile of
+    // many chunks pays for it once.  Eight keys per thread at a time.  (With
+    // diagnostics the selection does this: here it would cost a wave per SIMD.)
+    const int nqc = (end - start + EVAL_Q - 1) / EVAL_Q;
+    if (!EX && qc < nw) {
+        for (int k0 = 0; k0 < sc.W; k0 += NT * 8) {
+            uint64_t kk[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) kk[u] = st.key[sc.wbase + min(k0 + u * NT + tid, sc.W - 1)];
+            for (int j = qc; j < nw; j += nqc) {
+                const uint64_t kj = wkey[j];
+                int cnt = 0;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    if (k0 + u * NT < sc.W) cnt += count_before(kk[u], k0 + u * NT + tid, sc.W, kj, wbeg + j);
+                }
+                if (lane == 0) atomicAdd(&rk[j], cnt);
+            }
+        }
+    }
 
     // The next worker's e column and summaries travel in registers while the
     // current one is evaluated.  Plain loads of clamped (in-range) slots, masked
@@ -921,25 +1346,70 @@ __global__ __launch_bounds__(EVAL_THREADS) __attribute__((amdgpu_waves_per_eu(4)
     const int64_t brow = sc.bits_off + (int64_t)(((q0 - start) >> 6) + wave_id() + (lane % QPT) * (NT / 64)) * sc.W;
     uint64_t* const bdst = (lane < QPT ? st.bits_feas : st.bits_nt) + brow;
 
-    int cur = next_staged(Wi, nw, use_lb, 0);
+    // the wave's queries that some worker of the block can take (with EX only
+    // whether there are any, in anyb[0])
+    uint64_t anyb[QPT];
+#pragma unroll
+    for (int m = 0; m < QPT; ++m) anyb[m] = 0;
+    // Workers without a request are all alike where the capacity is one (no
+    // placement's prefill is counted on them either: its request would still be
+    // there); the block's first stands for the others, and the scenario's first
+    // is found by its rank.
+    uint64_t empty = 0;
+    if (!EX && sc.uniform_M) {
+        empty = ballot(lane < nw && wkey[min(lane, nw - 1)] == 0);  // (an empty worker's rank key)
+        empty &= empty - 1;
+    }
+    int cur = next_staged(Wi, nw, use_lb, empty, 0);
     if (cur < nw) pf = prefetch_worker(st, Wi[cur], sc.wbase + wbeg + cur, tid);
     while (cur < nw) {
         __syncthreads();  // the previous worker's readers of LBs / Ss are done
         stage_put(LBs, Ss, pf, tid, Wi[cur].n - Wi[cur].head, L);
         __syncthreads();
-        const int nxt = next_staged(Wi, nw, use_lb, cur + 1);
+        const int nxt = next_staged(Wi, nw, use_lb, empty, cur + 1);
         if (nxt < nw) pf = prefetch_worker(st, Wi[nxt], sc.wbase + wbeg + nxt, tid);
         eval_worker<MODE, EX, true, false>(st, sc, Wi[cur], wbeg + cur, tau, lin, lp, act, am, qd, e1, w1, e2, w2,
-                                           LBs, Ss, bdst);
+                                           anyb, LBs, Ss, bdst);
         cur = nxt;
     }
     // workers too large to stage: binary search over global memory
     for (int j0 = 0; j0 < nw; ++j0) {
         const WInfo wi = Wi[j0];
-        if (use_lb && wi.n - wi.head < STAGE_MAX) continue;
-        eval_worker<MODE, EX, false, TAB>(st, sc, wi, wbeg + j0, tau, lin, lp, act, am, qd, e1, w1, e2, w2, LBs, Ss,
-                                          bdst);
+        if ((use_lb && wi.n - wi.head < STAGE_MAX) || ((empty >> j0) & 1)) continue;
+        eval_worker<MODE, EX, false, TAB>(st, sc, wi, wbeg + j0, tau, lin, lp, act, am, qd, e1, w1, e2, w2, anyb, LBs,
+                                          Ss, bdst);
     }
+    // the tile's queries with a feasible worker, and the first of them
+    if (EX) {
+        // (from the wave's own bit words: where the tile is long and the cluster
+        // full, as in admission control, there are none, and the masks would cost
+        // the loop a wave per SIMD in registers)
+        if (anyb[0] != 0) {
+            __builtin_amdgcn_s_waitcnt(0);  // they have left
+            uint64_t v[QPT];
+#pragma unroll
+            for (int m = 0; m < QPT; ++m) {
+                const int g = ((q0 - start) >> 6) + wave_id() + m * (NT / 64);
+                const uint64_t* row = st.bits_feas + sc.bits_off + (int64_t)g * sc.W + wbeg;
+                v[m] = lane < nw ? __hip_atomic_load(row + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+            }
+#pragma unroll
+            for (int m = 0; m < QPT; ++m) anyb[m] = wave_or64(v[m]);
+        }
+    }
+    int32_t first = INT32_MAX;
+#pragma unroll
+    for (int m = 0; m < QPT; ++m) {
+        if (anyb[m] == 0) continue;  // wave-uniform
+        if (lane == 0)
+            atomicOr((unsigned long long*)&st.any[sc.any_off + ((q0 - start) >> 6) + wave_id() + m * (NT / 64)],
+                     (unsigned long long)anyb[m]);
+        if ((anyb[m] >> lane) & 1) first = min(first, q0 + chunk_at[m * NT + tid]);
+    }
+    first = wave_min32(first);
+    if (lane == 0 && first != INT32_MAX) atomicMin(&st.tinfo[s].first_pc, first);
+    __syncthreads();
+    if (!EX && wave_id() == 0) publish_ranks(st, sc, s, nw, wbeg, nqc, qc, rk, wkey, true);
     if (MODE >= 1 && EX) {  // near-tie margins feed only the diagnostics
         for (int j0 = 0; j0 < nw; ++j0)
             if (Wi[j0].nt_any) near_tie_words<MODE>(st, sc, Wi[j0], wbeg + j0, lin, lp, act, bdst);
@@ -955,7 +1425,303 @@ __global__ __launch_bounds__(EVAL_THREADS) __attribute__((amdgpu_waves_per_eu(4)
 }
 
 // ---------------------------------------------------------------------------------------------
-// Per-query selection over all workers of the scenario.
+// Pair evaluation of short tiles (at most SHORT_TILE queries: heartbeats cut the
+// tiles of a serving stream to the queries of one decode iteration).  A block of
+// k_eval is laid out for 1,024 queries and stages every worker's summaries
+// through LDS; with 15 to 100 queries nearly all of its lanes idle and the
+// staging is the cost.  Here a block takes one 64-query group and wpb workers, a
+// wave a quarter of them: a lane holds one query, finds its breakpoint slot by a
+// binary search of the worker's ends in LDS (workers below SHORT_STAGE requests,
+// which then need no table; larger ones through their tables) and reads the
+// slot's summaries from global memory, four workers at a time.  What bounds it:
+// the dependent reads of one block, so few workers per wave and many blocks.  With diagnostics (EX) the block also leaves, per
+// query, its two smallest KV excesses and its feasible and near-tie counts,
+// which the commit merges itself.
+constexpr int SHORT_SPAN = SHORT_WPB / (EVAL_THREADS / 64);  // workers per wave
+static_assert(SHORT_SPAN <= 64, "one lane per worker");
+
+// saturated to int32 (comparisons against other saturated values stay conservative)
+__device__ __forceinline__ int32_t sat32(int64_t x)
+{
+    return x > INT32_MAX ? INT32_MAX : (x < INT32_MIN ? INT32_MIN : (int32_t)x);
+}
+
+template <int MODE, bool EX>
+__global__ __launch_bounds__(EVAL_THREADS) void k_eval_short(State st)
+{
+    constexpr int NT = EVAL_THREADS, NWV = NT / 64;
+    __shared__ int32_t rk[SHORT_WPB];
+    __shared__ uint64_t wkey[SHORT_WPB];
+    __shared__ uint64_t anyw[NWV];
+    struct Two {
+        uint64_t k1, k2;
+        int32_t nfeas, ntcnt;
+    };
+    __shared__ Two two[NWV][64];
+    constexpr int U = 4;  // workers in flight
+    __shared__ int32_t ends[NWV][U][SHORT_STAGE];
+    const int s = find_scen<&Scen::eval_blk0>(st, blockIdx.x);
+    const Scen sc = st.scen[s];
+    const Ctl* cp = st.ctl + s;
+    const int32_t start = cp->start, Q = cp->Q;
+    const bool mine = cp->call == st.call;
+    if (st.qbad != nullptr && start == 0 && mine) {
+        // first round of a one-scenario call: check every query length of the
+        // call before the first commit can run (grid-stride over all queries)
+        bool bad = false;
+        for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < Q; i += (int64_t)gridDim.x * NT) {
+            const int32_t a = st.q_lin[i], p = st.q_lpred[i];
+            bad = bad || !(a >= 1 && p >= 1 && a <= (1 << 24) && p <= (1 << 24));
+        }
+        if (ballot(bad) != 0 && lane_id() == 0) atomicOr(st.qbad, 1);
+    }
+    if (cp->err || start >= Q || !mine) return;
+    const int32_t end = tile_end(start, Q, cp->T, cp->H, cp->since_hb, cp->hb_next);
+    const int local = blockIdx.x - sc.eval_blk0;
+    const int wb = local % sc.nblk, g = local / sc.nblk;
+    const int q0 = start + g * 64;
+    if (q0 >= end) return;
+    const int ngr = (end - start + 63) >> 6;
+    const int32_t tau = cp->tau, hb = cp->hb_index;
+    const int tid = threadIdx.x, lane = lane_id(), wv = wave_id();
+    const int wbeg = wb * sc.wpb, nw = min(sc.W, wbeg + sc.wpb) - wbeg;
+    // this wave's workers: w0 .. w0 + nk - 1, lane k holding worker k's figures
+    const int span = (nw + NWV - 1) / NWV;
+    const int w0 = wbeg + wv * span;
+    const int nk = max(0, min(span, wbeg + nw - w0));
+    const int gwk = sc.wbase + min(w0 + min(lane, max(nk - 1, 0)), sc.W - 1);
+    const int32_t fhead = st.head[gwk], fn = st.n[gwk], fM = st.M[gwk], flthr = st.lthr[gwk];
+    const int64_t fbase = st.slot_base[gwk] + fhead, fdq = st.dq_max[gwk];
+    const int32_t fB = fn - fhead;
+    if (tid < nw) {
+        rk[tid] = 0;
+        wkey[tid] = st.key[sc.wbase + wbeg + tid];
+    }
+    // the workers to evaluate (of those without a request, see k_eval, the wave's
+    // first stands for the others)
+    uint64_t left = nk > 0 ? ~0ull >> (64 - nk) : 0;
+    if (!EX && sc.uniform_M) {
+        const uint64_t empty = left & ballot(fB == 0);
+        left &= ~(empty & (empty - 1));
+    }
+    // this lane's query
+    const bool act = q0 + lane < end;
+    const int64_t qi = q_at(sc, min(q0 + lane, end - 1));
+    const int32_t lin = act ? st.q_lin[qi] : 1;
+    const int32_t lp = act ? max(st.q_lpred[qi], 1) : 1;  // (an invalid length fails the call)
+    const int64_t qD = ((int64_t)lin << sc.gs) + (int64_t)sc.gn * lp;
+    const uint32_t sq = (uint32_t)(lin - tau), eq = (uint32_t)(lp + tau);
+    const uint64_t am = ballot(act);
+    // the next workers (the last one again where fewer are left) and their first
+    // 64 ends, in flight early
+    int kx[U], kn = 0;
+    int32_t pre[U];
+    auto prefetch = [&]() {
+        kn = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            kn += left != 0 ? 1 : 0;
+            kx[u] = left != 0 ? __builtin_ctzll(left) : (u > 0 ? kx[u > 0 ? u - 1 : 0] : 0);
+            left &= left - 1;
+            pre[u] = (st.e + rdlane64s(fbase, kx[u]))[max(min(lane, rdlane(fB, kx[u]) - 1), 0)];
+        }
+    };
+    prefetch();
+    __syncthreads();
+    // Algorithm 1's rank of the block's workers at tile start (the number of
+    // workers that rank before it), shared out over the tile's groups
+    if (g < nw) {
+        for (int k0 = 0; k0 < sc.W; k0 += NT * 8) {
+            uint64_t kk[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) kk[u] = st.key[sc.wbase + min(k0 + u * NT + tid, sc.W - 1)];
+            for (int j = g; j < nw; j += ngr) {
+                const uint64_t kj = wkey[j];
+                int cnt = 0;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    if (k0 + u * NT < sc.W) cnt += count_before(kk[u], k0 + u * NT + tid, sc.W, kj, wbeg + j);
+                }
+                if (lane == 0) atomicAdd(&rk[j], cnt);
+            }
+        }
+    }
+    // workers whose tie bands some query of the group may lie in
+    uint64_t tied = 0;
+    if (EX && MODE >= 1) {
+        const int32_t qs = sat32(qD);
+        const int32_t qmin = wave_min32(act ? qs : INT32_MAX), qmax = wave_max32(act ? qs : INT32_MIN);
+        const int32_t lmin = wave_min32(act ? lin : INT32_MAX), lmax = wave_max32(act ? lin : INT32_MIN);
+        bool t = (qmax >= sat32(st.ntd_lo[gwk]) && qmin <= sat32(st.ntd_hi[gwk])) ||
+                 (lmax >= st.ntt_lo[gwk] && lmin <= st.ntt_hi[gwk]);
+        // (constraint (d) never runs with the integer near-tie sets, mode 2)
+        if (MODE == 1) t = t || (lmax >= st.ntp_lo[gwk] && lmin <= st.ntp_hi[gwk]);
+        tied = ballot(lane < nk && t);
+    }
+    uint64_t wf = 0, wn = 0;  // lane k: worker k's bit words
+    uint64_t anyf = 0;
+    int32_t nfeas = 0, ntcnt = 0;
+    int32_t e1 = INT32_MAX, w1 = -1, e2 = INT32_MAX, w2 = -1;
+    while (kn > 0) {  // (an empty worker's first end is never compared)
+        int k4[U];
+        const int n4 = kn;
+#pragma unroll
+        for (int u = 0; u < U; ++u) k4[u] = kx[u];
+        int at[U];  // first live slot ending at or after the query
+        int4 t[U];
+        int most = 0;  // of the workers staged
+        bool tables = false;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = k4[u];
+            const int B = rdlane(fB, k);
+            most = max(most, B < SHORT_STAGE ? B : 0);
+            tables = tables || B >= SHORT_STAGE;
+            ends[wv][u][lane] = pre[u];
+        }
+        for (int c = 64; c < most; c += 64) {
+            int32_t v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int k = k4[u];
+                v[u] = (st.e + rdlane64s(fbase, k))[max(min(c + lane, rdlane(fB, k) - 1), 0)];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) ends[wv][u][c + lane] = v[u];
+        }
+        prefetch();
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int u = 0; u < U; ++u) at[u] = 0;
+        // a binary search in LDS, the four workers' side by side
+        for (int step = most > 0 ? 1 << (31 - __builtin_clz(most)) : 0; step > 0; step >>= 1) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int B = rdlane(fB, k4[u]);
+                const int to = at[u] + step;
+                const int32_t v = ends[wv][u][min(to, SHORT_STAGE) - 1];
+                at[u] = (to <= B && B < SHORT_STAGE && v < (int32_t)eq) ? to : at[u];
+            }
+        }
+        if (tables) {
+            // larger workers: through their tables; past a table (or without one) the
+            // slot is searched from the table's last entry on
+            int len[U];
+            bool more = false;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int k = k4[u];
+                const int B = rdlane(fB, k);
+                const uint16_t* tb = st.lbt + (int64_t)(sc.wbase + w0 + k) * LB_MAX;
+                if (B >= SHORT_STAGE) at[u] = B < LB_SLOTS ? tb[min(lp, LB_MAX) - 1] / (int)sizeof(int4) : 0;
+                len[u] = (B >= LB_SLOTS || (B >= SHORT_STAGE && lp > LB_MAX)) ? B - at[u] : 0;
+                more = more || len[u] > 0;
+            }
+            while (ballot(more) != 0) {
+                more = false;
+                int32_t v[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    v[u] = (st.e + rdlane64s(fbase, k4[u]))[at[u] + (len[u] > 0 ? len[u] >> 1 : 0)];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int half = len[u] >> 1;
+                    const bool right = len[u] > 0 && v[u] < (int32_t)eq;
+                    at[u] = right ? at[u] + half + 1 : at[u];
+                    len[u] = right ? len[u] - half - 1 : half;
+                    more = more || len[u] > 0;
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = k4[u];
+            const int64_t base = rdlane64s(fbase, k);
+            t[u] = st.pms[base + at[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (u >= n4) break;
+            const int k = k4[u];
+            // every candidate is a KV demand with the query added, below 2^31:
+            // 32-bit wrap-around arithmetic gives it exactly
+            const int32_t a = (int32_t)((uint32_t)t[u].x + sq);
+            const int32_t c = (int32_t)((uint32_t)t[u].z + (uint32_t)t[u].w * eq + sq + eq);
+            int32_t peak = a > t[u].y ? a : t[u].y;
+            peak = peak > c ? peak : c;
+            const int32_t M = rdlane(fM, k);
+            uint64_t bf, bn = 0;
+            if (MODE >= 1) {
+                bf = am & ballot(peak <= M) & ballot(qD <= rdlane64s(fdq, k)) & ballot(lin <= rdlane(flthr, k));
+            } else {
+                const View v = load_view(st, sc.wbase + w0 + k, hb);
+                const Latency Lt = latency(sc, v, lin, lp, rdlane(fB, k) + 1);
+                bf = am & ballot(peak <= M) & ballot(Lt.dec_ok && Lt.ttft_ok);
+                bn = am & ballot(Lt.nt);
+            }
+            if (EX && MODE >= 1 && ((tied >> k) & 1)) {
+                const int gw = sc.wbase + w0 + k;
+                bool nt;
+                if (MODE == 2) {
+                    const uint64_t dd = (uint64_t)(qD - st.ntd_lo[gw]);
+                    const uint32_t dl = (uint32_t)(lin - st.ntt_lo[gw]);
+                    nt = (dd < 64 && ((st.ntd_mask[gw] >> dd) & 1)) || (dl < 64 && ((st.ntt_mask[gw] >> dl) & 1));
+                } else {
+                    const bool maybe = (qD >= st.ntd_lo[gw] && qD <= st.ntd_hi[gw]) ||
+                                       (lin >= st.ntt_lo[gw] && lin <= st.ntt_hi[gw]) ||
+                                       (lin >= st.ntp_lo[gw] && lin <= st.ntp_hi[gw]);
+                    nt = maybe && latency(sc, load_view(st, gw, hb), lin, lp, rdlane(fB, k) + 1).nt;
+                }
+                bn = am & ballot(nt);
+            }
+            anyf |= bf;
+            wf = lane == k ? bf : wf;
+            if (EX) {
+                wn = lane == k ? bn : wn;
+                nfeas += __builtin_amdgcn_inverse_ballot_w64(bf) ? 1 : 0;
+                ntcnt += __builtin_amdgcn_inverse_ballot_w64(bn) ? 1 : 0;
+                keep_two<true>(peak - M, w0 + k, e1, w1, e2, w2);
+            }
+        }
+    }
+    const int64_t row = sc.bits_off + (int64_t)g * sc.W;
+    if (lane < nk) {
+        st.bits_feas[row + w0 + lane] = wf;
+        if (EX) st.bits_nt[row + w0 + lane] = wn;
+    }
+    if (lane == 0) anyw[wv] = anyf;
+    if (EX) two[wv][lane] = Two{w1 < 0 ? ~0ull : ex_key(e1, w1), w2 < 0 ? ~0ull : ex_key(e2, w2), nfeas, ntcnt};
+    __syncthreads();
+    if (wv == 0) publish_ranks(st, sc, s, nw, wbeg, ngr, g, rk, wkey, !EX);
+    if (tid == 0) {
+        const uint64_t f = anyw[0] | anyw[1] | anyw[2] | anyw[3];
+        if (f != 0) {
+            atomicOr((unsigned long long*)&st.any[sc.any_off + g], (unsigned long long)f);
+            atomicMin(&st.tinfo[s].first_pc, q0 + __builtin_ctzll(f));
+        }
+    }
+    if (EX && wv == NWV - 1 && act) {
+        uint64_t a1 = ~0ull, a2 = ~0ull;
+        int32_t nf = 0, nt = 0;
+#pragma unroll
+        for (int v = 0; v < NWV; ++v) {
+            const Two x = two[v][lane];
+            merge_two(a1, a2, x.k1, x.k2);
+            nf += x.nfeas;
+            nt += x.ntcnt;
+        }
+        ulonglong2* out = st.part + sc.part_off + 2 * ((int64_t)wb * sc.pstride + g * 64 + lane);
+        out[0] = make_ulonglong2(a1, a2);
+        out[1] = make_ulonglong2((uint32_t)nf, (uint32_t)nt);
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Per-query summary over all workers of the scenario, for the diagnostics: how
+// many are feasible, how many have a near-tie margin, the two smallest KV
+// excesses.  A lane holds one query of a 64-query group; the waves of the group
+// share the workers.  Each non-zero bit word is added to the lanes' counts
+// straight from its mask.
 __global__ __launch_bounds__(SEL_THREADS) void k_select(State st)
 {
     const int s = find_scen<&Scen::sel_blk0>(st, blockIdx.x);
@@ -963,17 +1729,23 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(State st)
     Ctl* cp = st.ctl + s;
     const int32_t start = cp->start, Q = cp->Q;
     const int local = blockIdx.x - sc.sel_blk0;
-    if (cp->call != st.call) return;  // another call's control block (its tile record too)
-    const bool done = cp->err || start >= Q;
-    const int32_t end = done ? start : tile_end(start, Q, cp->T, cp->H, cp->since_hb, cp->hb_next);
-    const int parity = cp->round & 1;
-    if (local == 0 && threadIdx.x == 0) {
-        TileInfo* ti = st.tinfo + s;
-        ti->start = done ? Q : start;
-        ti->end = done ? Q : end;
-        ti->parity = parity;
+    if (cp->call != st.call) return;  // another call's control block
+    if (cp->err || start >= Q) return;
+    const int32_t end = tile_end(start, Q, cp->T, cp->H, cp->since_hb, cp->hb_next);
+    // Algorithm 1's rank order at tile start, for the commit: a worker's place is
+    // the number of workers that rank before it, counted by one wave per worker
+    for (int j = local * (SEL_THREADS / 64) + wave_id(); j < sc.W; j += sc.sel_n * (SEL_THREADS / 64)) {
+        const uint64_t kj = st.key[sc.wbase + j];
+        int cnt = 0;
+        for (int k0 = 0; k0 < sc.W; k0 += 64 * 8) {
+            uint64_t kk[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) kk[u] = st.key[sc.wbase + min(k0 + u * 64 + lane_id(), sc.W - 1)];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) cnt += count_before(kk[u], k0 + u * 64 + lane_id(), sc.W, kj, j);
+        }
+        if (lane_id() == 0) st.order[sc.wbase + cnt] = j;
     }
-    if (done) return;
     // waves of the block: sel_g of them per 64-query group, each scanning its
     // share of the workers
     constexpr int NWV = SEL_THREADS / 64;
@@ -990,25 +1762,13 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(State st)
     const bool act = live && q0 + lane < end;
     const int qi = (act && st.qorig != nullptr) ? start + st.qorig[slot] : q0 + lane;
 
-    uint64_t tkey[TOPK];
-    int32_t tw[TOPK];
-#pragma unroll
-    for (int k = 0; k < TOPK; ++k) { tkey[k] = 0; tw[k] = -1; }
-    int32_t nfeas = 0, ntcnt = 0, ntw = -1, ncand = 0;
-    bool efeas = false;
-    uint64_t ntkey = 0;
+    int32_t nfeas = 0, ntcnt = 0;
     // the group's 64 queries share one bit word per worker; 64 workers' words
     // are read at once and only workers with a set bit are visited
     const int64_t row = sc.bits_off + (int64_t)group * sc.W;
     const int span = ((sc.W + G * 64 - 1) / (G * 64)) * 64;  // workers per wave, whole batches
     const int wlo = live ? min(sc.W, slice * span) : 0;
     const int whi = live ? min(sc.W, wlo + span) : 0;
-    // Without diagnostics only the choice matters: near-tie words are not
-    // read, and the interchangeable empty workers of a uniform-capacity
-    // scenario are taken 64 at a time (an OR of their words); nfeas then only
-    // says whether some worker is feasible.
-    const bool diag = st.out_diag != nullptr;
-    const bool bulk_empty = !diag && sc.uniform_M;
     constexpr int UB = 8;  // 64-worker batches whose words are loaded together
     for (int g0 = wlo; g0 < whi; g0 += 64 * UB) {
         uint64_t fls[UB], nls[UB];
@@ -1017,59 +1777,21 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(State st)
             const int wl = g0 + u * 64 + lane;
             const bool in = wl < whi;
             fls[u] = in ? st.bits_feas[row + wl] : 0;
-            nls[u] = (in && diag) ? st.bits_nt[row + wl] : 0;
+            nls[u] = in ? st.bits_nt[row + wl] : 0;
         }
 #pragma unroll
         for (int u = 0; u < UB; ++u) {
-            const int wb0 = g0 + u * 64;
-            const uint64_t fl = fls[u], nl = nls[u];
-            uint64_t mask = ballot((fl | nl) != 0);
-            if (!mask) continue;
-            const int wl = wb0 + lane;
-            const uint64_t kl = wl < whi ? st.key[sc.wbase + wl] : 0;
-            if (bulk_empty) {
-                const uint64_t em = mask & ballot(kl == 0);
-                if (em) {
-                    const uint64_t any = wave_or64(((em >> lane) & 1) ? fl : 0);
-                    efeas = efeas | (((any >> lane) & 1) != 0);
-                    mask &= ~em;
-                }
-            }
-            while (mask) {
-                const int j = __ffsll((unsigned long long)mask) - 1;
-                mask &= mask - 1;
-                const uint64_t fw = rdlane64(fl, j);
-                const uint64_t nw = rdlane64(nl, j);
-                const uint64_t key = rdlane64(kl, j);
-                const int w = wb0 + j;
-                const bool f = (fw >> lane) & 1;
-                const bool nb = (nw >> lane) & 1;
-                nfeas += f ? 1 : 0;
-                // an empty worker has rank key 0; with uniform capacity all empty
-                // workers are alike and stand in one class
-                const bool cls = sc.uniform_M && key == 0;
-                efeas = efeas | (cls & f);
-                ncand += (f & !cls) ? 1 : 0;
-                topk_insert<TOPK>(tkey, tw, key, (f && !cls) ? w : -1);
-                ntcnt += nb ? 1 : 0;
-                const bool better = nb & ranks_before(key, w, ntkey, ntw);
-                ntkey = better ? key : ntkey;
-                ntw = better ? w : ntw;
-            }
+            for (uint64_t m = ballot(fls[u] != 0); m != 0; m &= m - 1)
+                nfeas += __builtin_amdgcn_inverse_ballot_w64(rdlane64(fls[u], __ffsll((unsigned long long)m) - 1)) ? 1 : 0;
+            for (uint64_t m = ballot(nls[u] != 0); m != 0; m &= m - 1)
+                ntcnt += __builtin_amdgcn_inverse_ballot_w64(rdlane64(nls[u], __ffsll((unsigned long long)m) - 1)) ? 1 : 0;
         }
     }
-    // the two smallest KV excesses feed only the diagnostics: each wave of
-    // the group merges its share of the worker blocks' two smallest keys (new
-    // first = smaller first; new second = min(larger first, smaller second))
+    // each wave of the group merges its share of the worker blocks' two
+    // smallest excess keys
     uint64_t a1 = ~0ull, a2 = ~0ull;
-    auto merge = [&](ulonglong2 p) {
-        const uint64_t lo = p.x < a1 ? p.x : a1;
-        const uint64_t hi = p.x < a1 ? a1 : p.x;
-        const uint64_t s2 = p.y < a2 ? p.y : a2;
-        a1 = lo;
-        a2 = hi < s2 ? hi : s2;
-    };
-    if (act && st.out_diag) {
+    auto merge = [&](ulonglong2 p) { merge_two(a1, a2, p.x, p.y); };
+    if (act) {
         const ulonglong2* prow = st.part + sc.part_off + slot;
         if (sc.nblk > 64 * G) {  // many worker blocks (short tiles over many workers): more reads in flight
 #pragma unroll 16
@@ -1079,87 +1801,43 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(State st)
             for (int b = slice; b < sc.nblk; b += G) merge(prow[(int64_t)b * sc.pstride]);
         }
     }
-    // merge the group's partial results into its first wave (lists by rank,
-    // counts summed, excess keys as above)
+    // merge the group's partial results into its first wave
     struct Part {
-        uint64_t tkey[TOPK];
-        int32_t tw[TOPK];
-        uint64_t ntkey, a1, a2;
-        int32_t ntw, nfeas, ncand, ntcnt, efeas, pad;
+        uint64_t a1, a2;
+        int32_t nfeas, ntcnt;
     };
     __shared__ Part parts[NWV][64];
     if (G > 1) {
-        if (slice > 0) {
-            Part& pt = parts[wv][lane];
-#pragma unroll
-            for (int k = 0; k < TOPK; ++k) { pt.tkey[k] = tkey[k]; pt.tw[k] = tw[k]; }
-            pt.ntkey = ntkey;
-            pt.ntw = ntw;
-            pt.nfeas = nfeas;
-            pt.ncand = ncand;
-            pt.ntcnt = ntcnt;
-            pt.efeas = efeas ? 1 : 0;
-            pt.a1 = a1;
-            pt.a2 = a2;
-        }
+        if (slice > 0) parts[wv][lane] = Part{a1, a2, nfeas, ntcnt};
         __syncthreads();
         if (slice > 0) return;
         for (int v = wv + 1; v < wv + G; ++v) {
-            const Part& pt = parts[v][lane];
-#pragma unroll
-            for (int k = 0; k < TOPK; ++k) topk_insert<TOPK>(tkey, tw, pt.tkey[k], pt.tw[k]);
-            const bool better = ranks_before(pt.ntkey, pt.ntw, ntkey, ntw);
-            ntkey = better ? pt.ntkey : ntkey;
-            ntw = better ? pt.ntw : ntw;
+            const Part pt = parts[v][lane];
             nfeas += pt.nfeas;
-            ncand += pt.ncand;
             ntcnt += pt.ntcnt;
-            efeas = efeas | (pt.efeas != 0);
-            const uint64_t lo = pt.a1 < a1 ? pt.a1 : a1;
-            const uint64_t hi = pt.a1 < a1 ? a1 : pt.a1;
-            const uint64_t s2 = pt.a2 < a2 ? pt.a2 : a2;
-            a1 = lo;
-            a2 = hi < s2 ? hi : s2;
+            merge(ulonglong2{pt.a1, pt.a2});
         }
-    }
-    if (!live) return;
-    int32_t ex1 = INT32_MAX, w1 = -1, ex2 = INT32_MAX, w2 = -1;
-    if (act && st.out_diag) {
-        ex_unpack(a1, ex1, w1);
-        ex_unpack(a2, ex2, w2);
     }
     if (!act) return;
     QSum q;
-#pragma unroll
-    for (int k = 0; k < TOPK; ++k) { q.tkey[k] = tkey[k]; q.tw[k] = tw[k]; }
-    q.ntkey = ntkey;
-    q.ntw = ntw;
+    q.nfeas = nfeas;
     q.ntcnt = ntcnt;
-    q.nfeas = bulk_empty ? ncand + (efeas ? 1 : 0) : nfeas;  // bulk: > 0 exactly when some worker is feasible
-    q.ncand = ncand;
-    q.efeas = efeas ? 1 : 0;
-    q.ex1 = ex1; q.w1 = w1;
-    q.ex2 = ex2; q.w2 = w2;
-    q.pad = 0;
-    st.qsum[sc.qsum_off + slot] = q;  // by tile position, as the bit words
-    if (q.nfeas > 0) {
-        atomicMin(&st.tinfo[s].first_pc[parity], qi);
-    } else if (st.qbad == nullptr || *st.qbad == 0) {
+    ex_unpack(a1, q.ex1, q.w1);
+    ex_unpack(a2, q.ex2, q.w2);
+    st.qsum[sc.qsum_off + (qi - start)] = q;
+    if (nfeas == 0 && (st.qbad == nullptr || *st.qbad == 0)) {
         // no feasible worker at tile start: rejected whatever the tile commits
         // before it.  These tile-start diagnostics are exact for the queries
-        // before the tile's first commit; the commit overwrites every query
-        // from its first feasible one on.
+        // before the tile's first commit; the commit overwrites the ones after.
         if (st.out_worker) st.out_worker[sc.out_off + q_at(sc, qi)] = -1;
-        if (st.out_diag) {
-            Diag d;
-            d.n_feasible = 0;
-            d.near_tie = ntcnt > 0 ? 1 : 0;
-            d.kv_peak_chosen = 0;
-            d.kv_excess_min = ex1;
-            d.ttft_chosen = 0.0;
-            d.tdec_chosen = 0.0;
-            st.out_diag[q_at(sc, qi)] = d;
-        }
+        Diag d;
+        d.n_feasible = 0;
+        d.near_tie = ntcnt > 0 ? 1 : 0;
+        d.kv_peak_chosen = 0;
+        d.kv_excess_min = q.ex1;
+        d.ttft_chosen = 0.0;
+        d.tdec_chosen = 0.0;
+        st.out_diag[q_at(sc, qi)] = d;
     }
 }
 
@@ -1180,21 +1858,32 @@ __global__ __launch_bounds__(256) void k_query_stats(const int32_t* lin, const i
         for (int s = 0; s < S; ++s) atomicCAS(&ctl[s].err, 0, DEV_EINVAL);
 }
 
-// Start of an ald_place_stream call (one scenario): the control block, the
-// tile record and a cleared query-error word (the first round's pair
-// evaluation checks the query lengths).  With gate >= 0 the call follows
-// asynchronous call `gate` and starts only if that call finished without an
-// error; otherwise the control block stays that call's, and every kernel of
-// this call finds it foreign and does nothing.
-__global__ void k_begin(Ctl c, TileInfo ti, Ctl* ctl, TileInfo* tinfo, int32_t* qbad, int32_t gate)
+// Start of an ald_place_stream call (one scenario, one block): the control
+// block, the tile record, the group words and a cleared query-error word (the
+// first round's pair evaluation checks the query lengths).  With gate >= 0 the
+// call follows asynchronous call `gate` and starts only if that call finished
+// without an error; otherwise the control block stays that call's, and every
+// kernel of this call finds it foreign and does nothing.
+__global__ __launch_bounds__(256) void k_begin(Ctl c, TileInfo ti, Ctl* ctl, TileInfo* tinfo, int32_t* qbad,
+                                               int32_t gate, uint64_t* any, int64_t words)
 {
     if (gate >= 0) {
         const Ctl o = *ctl;
         if (o.call != gate || o.err || o.start < o.Q) return;
+        __syncthreads();  // every thread has read it
     }
-    *ctl = c;
-    *tinfo = ti;
-    *qbad = 0;
+    for (int64_t k = threadIdx.x; k < words; k += 256) any[k] = 0;
+    if (threadIdx.x == 0) {
+        *ctl = c;
+        *tinfo = ti;
+        *qbad = 0;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_clear(uint64_t* any, int64_t words)
+{
+    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (k < words) any[k] = 0;
 }
 
 // The outcome of an asynchronous call with no queries.
@@ -1267,10 +1956,14 @@ hipError_t launch_ingest(const State& st, int32_t W, const int64_t* res_off, con
     return hipGetLastError();
 }
 
-hipError_t launch_build(const State& st, hipStream_t stream, int mode)
+hipError_t launch_build(const State& st, hipStream_t stream, int mode, int need, bool small)
 {
-    const int blocks = mode == 1 ? st.S * MAX_DIRTY : st.NW;
-    hipLaunchKernelGGL(k_build, dim3(blocks), dim3(BUILD_THREADS), 0, stream, st, mode);
+    const int workers = mode == 1 ? st.S * MAX_DIRTY : st.NW;
+    if (small)
+        hipLaunchKernelGGL(k_build_small, dim3((workers + SMALL_WAVES - 1) / SMALL_WAVES), dim3(64 * SMALL_WAVES), 0,
+                           stream, st, mode, need);
+    else
+        hipLaunchKernelGGL(k_build, dim3(workers), dim3(BUILD_THREADS), 0, stream, st, mode, need);
     return hipGetLastError();
 }
 
@@ -1278,6 +1971,19 @@ hipError_t launch_eval(const State& st, int32_t blocks, int mode, hipStream_t st
 {
     const bool ex = st.out_diag != nullptr;
     const dim3 g(blocks), b(EVAL_THREADS);
+    if (st.brief) {
+        if (mode >= 2) {
+            if (ex) hipLaunchKernelGGL((k_eval_short<2, true>), g, b, 0, stream, st);
+            else hipLaunchKernelGGL((k_eval_short<2, false>), g, b, 0, stream, st);
+        } else if (mode == 1) {
+            if (ex) hipLaunchKernelGGL((k_eval_short<1, true>), g, b, 0, stream, st);
+            else hipLaunchKernelGGL((k_eval_short<1, false>), g, b, 0, stream, st);
+        } else {
+            if (ex) hipLaunchKernelGGL((k_eval_short<0, true>), g, b, 0, stream, st);
+            else hipLaunchKernelGGL((k_eval_short<0, false>), g, b, 0, stream, st);
+        }
+        return hipGetLastError();
+    }
     if (mode == 3) {
         if (ex) hipLaunchKernelGGL((k_eval<2, true, true>), g, b, 0, stream, st);
         else hipLaunchKernelGGL((k_eval<2, false, true>), g, b, 0, stream, st);
@@ -1322,9 +2028,16 @@ hipError_t launch_query_stats(const int32_t* lin, const int32_t* lpred, int32_t 
 }
 
 hipError_t launch_begin(const Ctl& c, const TileInfo& ti, Ctl* ctl, TileInfo* tinfo, int32_t* qbad, int32_t gate,
-                        hipStream_t stream)
+                        uint64_t* any, int64_t words, hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_begin, dim3(1), dim3(1), 0, stream, c, ti, ctl, tinfo, qbad, gate);
+    hipLaunchKernelGGL(k_begin, dim3(1), dim3(256), 0, stream, c, ti, ctl, tinfo, qbad, gate, any, words);
+    return hipGetLastError();
+}
+
+hipError_t launch_clear(uint64_t* any, int64_t words, hipStream_t stream)
+{
+    if (words == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_clear, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, stream, any, words);
     return hipGetLastError();
 }
 

@@ -24,8 +24,9 @@ __global__ __launch_bounds__(MOVE_THREADS) void k_move(State st, MoveArgs a)
     const int s = find_scen_by_worker(st, gw);
     const Scen sc = st.scen[s];
     const int64_t base = st.slot_base[gw];
-    const int head = st.head[gw], n = st.n[gw], cap = st.cap[gw];
-    int B = n - head;
+    const int head = st.head[gw], n = st.n[gw], cap = st.cap[gw], tn = st.tn[gw];
+    const int B0 = n - head;  // sorted requests; tn more were appended by the last commit
+    int B = B0 + tn;
     const int nrm = mw.rm1 - mw.rm0, nin = mw.in1 - mw.in0;
     // the window's prefill sums must hold every request given up
     int64_t rs1 = 0, rs2 = 0;
@@ -41,11 +42,39 @@ __global__ __launch_bounds__(MOVE_THREADS) void k_move(State st, MoveArgs a)
         if (lane == 0) raise_error(a.err, nrm > 0 && B - nrm + nin <= cap ? DEV_EINVAL : DEV_ESLOTS);
         return;
     }
-    for (int k = lane; k < B; k += MOVE_THREADS) {
+    for (int k = lane; k < B0; k += MOVE_THREADS) {
         E[k] = st.e[base + head + k];
         S[k] = st.s[base + head + k];
     }
     __syncthreads();
+    B = B0;
+    // put (e, sv) after every entry with an end at or before it
+    auto insert = [&](int32_t e, int32_t sv) {
+        int cnt = 0;  // entries with E <= e (the columns are sorted by end)
+        for (int k0 = 0; k0 < B; k0 += MOVE_THREADS) cnt += __popcll(ballot(k0 + lane < B && E[k0 + lane] <= e));
+        for (int k0 = B - 1 - ((B - 1 - cnt) % MOVE_THREADS + MOVE_THREADS) % MOVE_THREADS; k0 >= cnt;
+             k0 -= MOVE_THREADS) {
+            const int k = k0 + lane;  // lanes shift entries k -> k + 1, from the top chunk down
+            const bool in = k >= cnt && k < B;
+            const int32_t oe = in ? E[k] : 0, os = in ? S[k] : 0;
+            __syncthreads();
+            if (in) {
+                E[k + 1] = oe;
+                S[k + 1] = os;
+            }
+            __syncthreads();
+        }
+        if (lane == 0) {
+            E[cnt] = e;
+            S[cnt] = sv;
+        }
+        __syncthreads();
+        B += 1;
+    };
+    for (int t = 0; t < tn; ++t) {
+        const int p = n + t > cap ? n + t - (cap + 1) : n + t;
+        insert(st.e[base + p], st.s[base + p]);
+    }
     // removals: the first matching entry, then the tail moves down one place
     for (int r = mw.rm0; r < mw.rm1; ++r) {
         const int32_t e = a.lpred[r] + a.tau, sv = a.lin[r] - a.tau;
@@ -71,30 +100,7 @@ __global__ __launch_bounds__(MOVE_THREADS) void k_move(State st, MoveArgs a)
         }
         B -= 1;
     }
-    // insertions: after every entry with an end at or before the new one
-    for (int r = mw.in0; r < mw.in1; ++r) {
-        const int32_t e = a.lpred[r] + a.tau, sv = a.lin[r] - a.tau;
-        int cnt = 0;  // entries with E <= e (the columns are sorted by end)
-        for (int k0 = 0; k0 < B; k0 += MOVE_THREADS) cnt += __popcll(ballot(k0 + lane < B && E[k0 + lane] <= e));
-        for (int k0 = B - 1 - ((B - 1 - cnt) % MOVE_THREADS + MOVE_THREADS) % MOVE_THREADS; k0 >= cnt;
-             k0 -= MOVE_THREADS) {
-            const int k = k0 + lane;  // lanes shift entries k -> k + 1, from the top chunk down
-            const bool in = k >= cnt && k < B;
-            const int32_t oe = in ? E[k] : 0, os = in ? S[k] : 0;
-            __syncthreads();
-            if (in) {
-                E[k + 1] = oe;
-                S[k + 1] = os;
-            }
-            __syncthreads();
-        }
-        if (lane == 0) {
-            E[cnt] = e;
-            S[cnt] = sv;
-        }
-        __syncthreads();
-        B += 1;
-    }
+    for (int r = mw.in0; r < mw.in1; ++r) insert(a.lpred[r] + a.tau, a.lin[r] - a.tau);
     if (!a.apply) return;
     const int nh = head + B <= cap ? head : 0;
     for (int k = lane; k < B; k += MOVE_THREADS) {
@@ -104,6 +110,7 @@ __global__ __launch_bounds__(MOVE_THREADS) void k_move(State st, MoveArgs a)
     if (lane == 0) {
         st.head[gw] = nh;
         st.n[gw] = nh + B;
+        st.tn[gw] = 0;
         int64_t s1 = cur ? st.S1[gw] : 0, s2 = cur ? st.S2[gw] : 0;
         s1 -= rs1;
         s2 -= rs2;
