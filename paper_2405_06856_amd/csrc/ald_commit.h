@@ -28,14 +28,19 @@ namespace ald {
 // worker's sorted columns in HBM (st.tn counts these) and updates the sums; the
 // build kernel of the next round sorts the appended requests in.
 //
-// What bounds it: the chain of decisions (one wave, no parallelism over
-// queries), so instructions and round trips per decision.  Measured per
-// placed query, 256-scenario sweep (tiles of 1,024, no diagnostics): see the
-// figures beside the launch.
+// What bounds it: the chain of decisions (one wave, no parallelism over queries), so
+// instructions, taken branches and round trips per decision.  Hence one straight
+// block of about 125 instructions for the decisions that need nothing rare,
+// single-lane changes by selects and v_writelane, stores only when a group ends,
+// and ties told apart by 20 leading bits of the key.  Measured in cycles of the
+// deciding wave: 600 to 700 per decision of that block (2,000 as one loop over
+// every case), 2,800 to 5,300 where a scan is needed.  With diagnostics the exact
+// peaks of the placements, 1,000 cycles each, are taken by all waves of the
+// block when the group ends.
 
 constexpr int DBITS_W = 2048;   // changed-worker bitmap words in LDS: scenarios of up to 65536 workers
 constexpr int ORDER_W = 4096;   // workers whose rank order is kept in LDS
-constexpr int POOL = 14336;     // pool entries (8 B each) for changed workers' columns
+constexpr int POOL = 12800;     // pool entries (8 B each) for changed workers' columns
 constexpr int POOL_SLACK = 48;  // entries a copied worker may grow by before it is copied again
 static_assert(POOL >= HOT + POOL_SLACK, "the largest worker fits the pool");
 
@@ -45,6 +50,8 @@ __device__ __forceinline__ void wave_sync() { __builtin_amdgcn_wave_barrier(); }
 
 // Branch hints: the decision loop is one wave's instruction stream, and every
 // taken branch over a block that hardly ever runs stalls it.
+// (a function of its own could not read the kernel's arguments)
+#define ALD_INLINE __attribute__((always_inline))
 #define ALD_LIKELY(x) __builtin_expect(!!(x), 1)
 #define ALD_RARELY(x) __builtin_expect(!!(x), 0)
 
@@ -67,16 +74,24 @@ __device__ __forceinline__ uint64_t uni(uint64_t x)
            (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)(uint32_t)x);
 }
 
+// The leading bits of a rank key, in its order: the high word of its value as a
+// double (20 bits after the leading one; distinct keys hardly ever share them).
+__device__ __forceinline__ uint32_t key_lead(uint64_t key)
+{
+    return (uint32_t)(__builtin_bit_cast(uint64_t, (double)key) >> 32);
+}
+
 // The lane of the non-empty mask m whose (key, worker) ranks first by Algorithm
-// 1's order.  The keys' high words nearly always decide.
-__device__ __forceinline__ int best_lane(uint64_t m, uint64_t key, int32_t w)
+// 1's order (lead = key_lead(key), which nearly always decides).
+__device__ __forceinline__ int best_lane(uint64_t m, uint32_t lead, uint64_t key, int32_t w)
 {
     if ((m & (m - 1)) == 0) return first_lane(m);
-    const uint32_t hi = (uint32_t)(key >> 32);
-    const uint32_t hm = wave_max_u32(in_mask(m) ? hi : 0u);
-    m &= ballot(hi == hm);
+    const uint32_t lm0 = wave_max_u32(in_mask(m) ? lead : 0u);
+    m &= ballot(lead == lm0);
     if (ALD_RARELY((m & (m - 1)) != 0)) {
-        const uint32_t lo = (uint32_t)key;
+        const uint32_t hi = (uint32_t)(key >> 32), lo = (uint32_t)key;
+        const uint32_t hm = wave_max_u32(in_mask(m) ? hi : 0u);
+        m &= ballot(hi == hm);
         const uint32_t lm = wave_max_u32(in_mask(m) ? lo : 0u);
         m &= ballot(lo == lm);
         if (m & (m - 1)) {
@@ -87,29 +102,26 @@ __device__ __forceinline__ int best_lane(uint64_t m, uint64_t key, int32_t w)
     return first_lane(m);
 }
 
-// The worker a lane holds.
+// The worker a lane holds: what every decision reads (the rest is in
+// CommitLDS).  Single lanes are changed by v_writelane or a select, without a
+// branch: a branch that changes some of these leaves the compiler copying all of
+// them between registers at every decision.
 struct Slot {
     int32_t w;       // scenario-local index, -1 = none
-    int32_t rk;      // its place in the tile-start rank order
     int32_t B;       // live requests, appended ones included
-    int32_t tn;      // requests appended in this tile
-    int32_t head, n, M, cap;
+    int32_t room;    // requests it can still take
+    int32_t M;
     // Bounds of its KV peak without a new query: at most M - slack; its demand at
     // end iteration loe is at least M - loe - flo (so with a query that is alive
     // then, sq + loe more).
     int32_t slack, flo, loe;
-    int32_t lgn;     // entries in its constraint-(d) log
-    int32_t off, room;  // its columns in the LDS pool (when copied): first entry, entries reserved
-    int64_t base;    // first slot
-    int32_t *ep, *sp;  // the slot range's columns
-    int64_t SC, SR;
     uint64_t key;
+    uint32_t lead;   // key_lead(key)
     // sums as fp64 (integers below 2^53 and multiples of 2^-8 below 2^31: exact)
     double DS;       // sum of D = 2^-gs * State::DS
     double S1, S2;   // TTFT sums of this heartbeat
     double rhs;
     double dlim;     // constraint (d)'s limit, fixed within a heartbeat (no ongoing request joins or leaves)
-    double phi;      // its slack gain: a request placed now logs slack - phi = -phi
 };
 
 // The kernel's arguments and its scenario, read where they are needed through a
@@ -151,17 +163,51 @@ __device__ __forceinline__ T in_vgpr(T x)
     return x;
 }
 
+// Waves per scenario: with diagnostics every placement needs its worker's exact KV
+// peak, which no later decision waits for; the other waves compute them.
+constexpr int commit_waves(bool diag) { return diag ? 8 : 1; }
+
 struct CommitLDS {
     int32_t cw[64], cr[64];  // untouched workers picked for the free lanes: index, rank
     uint64_t cword[64];      // and bit word
     int32_t over_w, over_r;  // the first one there was no lane for
+    // of the lanes' workers: place in the tile-start rank order, slot range and
+    // the sorted live slots in it at tile start, log entries and slack gain
+    // (constraint (d): a request placed now logs slack - phi = -phi)
+    int64_t base[64];
+    int32_t rk[64], head[64], n[64], cap[64], lgn[64];
+    double phi[64];
+    // and what the tile's requests add to their sums of c and r
+    uint64_t dsc[64], dsr[64];
+    // their columns in the pool (when copied): first entry, entries there is room
+    // for, entries there are (the worker's first so many requests)
+    int32_t off[64], room[64], have[64];
+    // the changed workers, when dirty_w was last used (note_dirty)
     int32_t dw[MAX_DIRTY];
     uint32_t dbits[DBITS_W];
     int32_t order[ORDER_W];
     int32_t pe[POOL], ps[POOL];
 };
 
-// Has worker w (scenario-local) changed in this tile?  (any lane, any w)
+// With diagnostics: what the waves of the block exchange.
+struct PeakLDS {
+    // the workers (by lane) whose placements of this group have no peak yet; 0: the
+    // tile is done
+    uint64_t jobs, fetch;  // fetch: of these, the ones whose columns must be copied first
+    int32_t rl[64], rB[64], lin[64], lp[64];  // the group's placements (as in the kernel's registers)
+    int32_t B[64];         // the workers' requests
+    int32_t peak[64];      // results: each query's peak
+    int32_t last[64];      // and each worker's peak after its last one
+    double tt[64], td[64];  // the choices' prefill and decode times
+    // short tiles: the waves' shares of the worker blocks' results
+    struct Two {
+        uint64_t a1, a2;
+        int32_t nfeas, ntcnt;
+    } two[commit_waves(true)][64];
+};
+
+// Has worker w (scenario-local) changed in this tile?  (any lane, any w; nd
+// workers listed by note_dirty)
 __device__ __forceinline__ bool dirty_w(const CommitLDS& L, int W, int nd, int w)
 {
     if (W <= DBITS_W * 32) return (L.dbits[w >> 5] >> (w & 31)) & 1u;
@@ -275,6 +321,62 @@ __device__ __forceinline__ Peak wave_kv_peak(const int32_t* e, const int32_t* s,
     return r;
 }
 
+// The same with the query's request put into the columns (room for B + 1): its
+// peak with the query.
+__device__ __forceinline__ int32_t wave_peak_insert(int32_t* e, int32_t* s, int B, int32_t sq, int32_t eq)
+{
+    const int lane = lane_id();
+    if (ALD_RARELY(B > 128)) {
+        const int32_t with = wave_kv_peak(e, s, B, sq, eq).with;
+        lds_sorted_insert(e, s, B, eq, sq);
+        return with;
+    }
+    int32_t ek[2], sk[2], inc[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const int k = min(c * 64 + lane, max(B - 1, 0));
+        ek[c] = e[k];
+        sk[c] = s[k];
+    }
+    uint64_t later[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const bool in = c * 64 + lane < B;
+        sk[c] = in ? sk[c] : 0;
+        later[c] = ballot(in) & ballot(ek[c] >= eq);
+        inc[c] = wave_incl_scan(sk[c], 0, Add32());
+    }
+    const int ahead = later[0] != 0 ? first_lane(later[0]) : (later[1] != 0 ? 64 + first_lane(later[1]) : B);
+    const int32_t all0 = rdlane(inc[0], 63), all1 = rdlane(inc[1], 63);
+    const int32_t run0 = all1 + all0 - inc[0] + sk[0], run1 = all1 - inc[1] + sk[1];  // sums of s over slots >= k
+    const int32_t later_s = later[0] != 0 ? rdlane(run0, first_lane(later[0]))
+                                          : (later[1] != 0 ? rdlane(run1, first_lane(later[1])) : 0);
+    // (wrap-around arithmetic: the demands themselves are below 2^31)
+    int32_t best = (int32_t)((uint32_t)later_s + (uint32_t)(B - ahead) * (uint32_t)eq + (uint32_t)sq + (uint32_t)eq);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const int k = c * 64 + lane;
+        const uint32_t P = (uint32_t)(c ? run1 : run0) + (uint32_t)(B - k) * (uint32_t)ek[c];
+        const int32_t val = (int32_t)(P + (ek[c] < eq ? (uint32_t)sq + (uint32_t)ek[c] : 0u));
+        best = k < B && val > best ? val : best;
+    }
+    wave_sync();
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const int k = c * 64 + lane;
+        if (k >= ahead && k < B) {
+            e[k + 1] = ek[c];
+            s[k + 1] = sk[c];
+        }
+    }
+    if (lane == 0) {
+        e[ahead] = eq;
+        s[ahead] = sq;
+    }
+    wave_sync();
+    return wave_max32(best);
+}
+
 // A fresh read of data that another lane of this wave wrote earlier in the
 // launch (the caller has waited for the wave's stores).
 __device__ __forceinline__ int32_t coherent(const int32_t* p)
@@ -290,22 +392,115 @@ __device__ __forceinline__ void publish_ctl(const Ctl& c)
     if (st->status != nullptr) *gptr(st->status) = ctl_status(c);
 }
 
-template <bool DIAG, bool USE_D>
-__global__ __launch_bounds__(COMMIT_THREADS) void k_commit(State)
+// Copies the columns of the worker of lane j into the pool (its sorted slots at
+// tile start).  One wave.
+__device__ __forceinline__ void copy_columns(CommitLDS& L, int j)
 {
     constexpr int NT = COMMIT_THREADS;
-    const int lane = threadIdx.x;
+    const int lane = lane_id();
+    const StateArg st = state_arg();
+    const int off = uni(L.off[j]), head = uni(L.head[j]), B0 = uni(L.n[j]) - head;
+    const int64_t base = (int64_t)uni((uint64_t)L.base[j]);
+    const int32_t* const ge = gptr(st->e) + base + head;
+    const int32_t* const gs_ = gptr(st->s) + base + head;
+    for (int k0 = 0; k0 < B0; k0 += 4 * NT) {
+        int32_t ve[4], vs[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int k = min(k0 + u * NT + lane, B0 - 1);
+            ve[u] = ge[k];
+            vs[u] = gs_[k];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int k = k0 + u * NT + lane;
+            if (k < B0) {
+                L.pe[off + k] = ve[u];
+                L.ps[off + k] = vs[u];
+            }
+        }
+    }
+    if (lane == 0) L.have[j] = B0;
+    wave_sync();
+}
+
+// Brings the columns of lane j's worker (in the pool) up to its B requests: those
+// of earlier groups from HBM, this group's from its lanes (rl, rB, lin, lp as
+// in the kernel), with diagnostics computing their peaks on the way; the last of
+// these is returned (-1: none).  One wave; the earlier groups' stores have left.
+template <bool DIAG>
+__device__ __forceinline__ int32_t advance_columns(CommitLDS& L, int32_t* peak, int j, int B, int32_t tau, int32_t rl,
+                                                   int32_t rB, int32_t lin, int32_t lp)
+{
+    const StateArg st = state_arg();
+    const int lane = lane_id();
+    const int off = uni(L.off[j]);
+    int at = uni(L.have[j]);
+    int32_t with = -1;
+    if (at >= B) return with;
+    const uint64_t here = ballot(rl == j) & ballot(rB >= at);
+    const int upto = B - __popcll(here);
+    if (ALD_RARELY(at < upto)) {
+        const int head = uni(L.head[j]), cap = uni(L.cap[j]);
+        const int64_t base = (int64_t)uni((uint64_t)L.base[j]);
+        for (; at < upto; ++at) {
+            int p = head + at;
+            p = p > cap ? p - (cap + 1) : p;
+            const int32_t x = coherent(gptr(st->e) + base + p), y = coherent(gptr(st->s) + base + p);
+            lds_sorted_insert(L.pe + off, L.ps + off, at, uni(x), uni(y));
+        }
+    }
+    for (uint64_t m = here; m != 0; m &= m - 1, ++at) {
+        const int p = first_lane(m);
+        const int32_t eq = rdlane(lp, p) + tau, sq = rdlane(lin, p) - tau;
+        if (DIAG) {
+            with = wave_peak_insert(L.pe + off, L.ps + off, at, sq, eq);
+            if (lane == 0) peak[p] = with;
+        } else {
+            lds_sorted_insert(L.pe + off, L.ps + off, at, eq, sq);
+        }
+    }
+    if (lane == 0) L.have[j] = B;
+    wave_sync();
+    return with;
+}
+
+// This wave's share of the group's jobs (PeakLDS).
+__device__ __forceinline__ void run_jobs(CommitLDS& L, PeakLDS& P, int wave, int32_t tau)
+{
+    const int lane = lane_id();
+    const int32_t rl = P.rl[lane], rB = P.rB[lane], lin = P.lin[lane], lp = P.lp[lane];
+    const uint64_t jobs = uni(P.jobs), fetch = uni(P.fetch);
+    int i = 0;
+    uint64_t mine = 0;
+    for (uint64_t m = jobs; m != 0; m &= m - 1, ++i)
+        if (i % commit_waves(true) == wave) mine |= m & (0 - m);
+    for (uint64_t m = mine & fetch; m != 0; m &= m - 1) copy_columns(L, first_lane(m));
+    for (uint64_t m = mine; m != 0; m &= m - 1) {
+        const int j = first_lane(m);
+        const int32_t with = advance_columns<true>(L, P.peak, j, uni(P.B[j]), tau, rl, rB, lin, lp);
+        if (lane == 0) P.last[j] = with;
+    }
+}
+
+template <bool DIAG, bool USE_D>
+__global__ __launch_bounds__(COMMIT_THREADS * commit_waves(DIAG)) void k_commit(State)
+{
+    constexpr int NT = COMMIT_THREADS;  // the deciding wave
+    constexpr int NWV = commit_waves(DIAG);
+    const int lane = lane_id();
+    const int wave = uni(wave_id());
     Ctl* const cp = gptr(state_arg()->ctl) + blockIdx.x;
     const Ctl c = *cp;
     {
         const StateArg st = state_arg();
         if (c.call != st->call) {  // another call's control block: this call was blocked
-            if (st->status != nullptr && lane == 0) *gptr(st->status) = ALD_EBLOCKED;
+            if (st->status != nullptr && threadIdx.x == 0) *gptr(st->status) = ALD_EBLOCKED;
             return;
         }
         const bool qbad = gptr(st->qbad) != nullptr && *gptr(st->qbad) != 0;
         if (qbad || c.err || c.start >= c.Q) {
-            if (lane == 0) {
+            if (threadIdx.x == 0) {
                 Ctl o = c;
                 if (qbad) {  // an invalid query length: nothing is written
                     o.err = DEV_EINVAL;
@@ -325,19 +520,57 @@ __global__ __launch_bounds__(COMMIT_THREADS) void k_commit(State)
     const bool sorted = gptr(state_arg()->qpos) != nullptr;
 
     __shared__ CommitLDS L;
+    __shared__ std::conditional_t<DIAG, PeakLDS, char> peak_lds;
+    PeakLDS& P = reinterpret_cast<PeakLDS&>(peak_lds);  // (only touched with diagnostics)
     const bool lds_order = W <= ORDER_W;
     if (fpc < end) {
         if (W <= DBITS_W * 32)
-            for (int k = lane; k < (W + 31) / 32; k += NT) L.dbits[k] = 0u;
+            for (int k = threadIdx.x; k < (W + 31) / 32; k += NT * NWV) L.dbits[k] = 0u;
         if (lds_order) {
             const int32_t* const order = gptr(state_arg()->order) + scen_arg()->wbase;
-            for (int k0 = 0; k0 < W; k0 += 4 * NT) {
+            for (int k0 = 0; k0 < W; k0 += 4 * NT * NWV) {
                 int32_t v[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) v[u] = order[min(k0 + u * NT + lane, W - 1)];
+                for (int u = 0; u < 4; ++u) v[u] = order[min(k0 + u * NT * NWV + (int)threadIdx.x, W - 1)];
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (k0 + u * NT + lane < W) L.order[k0 + u * NT + lane] = v[u];
+                for (int u = 0; u < 4; ++u) {
+                    const int k = k0 + u * NT * NWV + threadIdx.x;
+                    if (k < W) L.order[k] = v[u];
+                }
+            }
+        }
+    }
+    // short tiles with diagnostics: the commit merges the worker blocks' results
+    // per query itself and writes every query's diagnostics (else the selection
+    // wrote those of the queries that no worker can take).  shares waves take a
+    // group's blocks between them.
+    const bool brief = DIAG && state_arg()->brief != 0;
+    static_assert(SHORT_TILE <= 64 * commit_waves(true), "a wave per group at least");
+    const int shares = NWV / max(min(groups, NWV), 1);
+    if (brief && wave < groups * shares) {
+        const int64_t stride = scen_arg()->pstride;
+        const int t = wave / shares * 64 + lane;
+        const ulonglong2* row = gptr(state_arg()->part) + scen_arg()->part_off + 2 * (int64_t)(t < end - start ? t : 0);
+        PeakLDS::Two r{~0ull, ~0ull, 0, 0};
+        const int nblk = scen_arg()->nblk;
+#pragma unroll 8
+        for (int b = wave % shares; b < nblk; b += shares) {
+            const ulonglong2 x = row[2 * b * stride], y = row[2 * b * stride + 1];
+            merge_two(r.a1, r.a2, x.x, x.y);
+            r.nfeas += (int32_t)y.x;
+            r.ntcnt += (int32_t)y.y;
+        }
+        P.two[wave][lane] = r;
+    }
+    if (wave == 0) L.dsc[lane] = L.dsr[lane] = 0;
+    if (NWV > 1) {
+        __syncthreads();
+        if (wave != 0) {
+            for (;;) {  // the deciding wave posts jobs until the tile is done
+                __syncthreads();
+                if (uni(P.jobs) == 0) return;
+                run_jobs(L, P, wave, tau);
+                __syncthreads();
             }
         }
     }
@@ -348,12 +581,11 @@ __global__ __launch_bounds__(COMMIT_THREADS) void k_commit(State)
     int pool_at = 0;
     Slot a;
     a.w = -1;
-    a.rk = a.B = a.tn = a.head = a.n = a.M = a.cap = a.slack = a.flo = a.lgn = a.off = a.room = 0;
+    a.B = a.room = a.M = a.slack = a.flo = 0;
     a.loe = INT32_MAX;
-    a.base = a.SC = a.SR = 0;
-    a.ep = a.sp = nullptr;
     a.key = 0;
-    a.DS = a.S1 = a.S2 = a.rhs = a.phi = 0.0;
+    a.lead = 0;
+    a.DS = a.S1 = a.S2 = a.rhs = 0.0;
     a.dlim = INFINITY;
     // the model's coefficients, in vector registers (the decision loop has no
     // scalar registers to spare)
@@ -365,114 +597,114 @@ __global__ __launch_bounds__(COMMIT_THREADS) void k_commit(State)
     const uint32_t gs = in_vgpr(scen_arg()->gs);
 
     auto rhs_of = [&](int B) { return theta * (dmax - c2 * (double)(B + 1)); };
-    // this lane's worker at tile start (its columns and sums are as built)
-    auto load_slot = [&](int w, int rk) {
+    // the lanes where `in` holds take worker w (any valid index elsewhere) as at
+    // tile start (its columns and sums are as built)
+    auto load_slot = [&](bool in, int w, int rk) ALD_INLINE {
         const StateArg st = state_arg();
         const int gw = scen_arg()->wbase + w;
-        a.w = w;
-        a.rk = rk;
-        a.tn = 0;
-        a.n = gptr(st->n)[gw];
-        a.head = gptr(st->head)[gw];
-        a.M = gptr(st->M)[gw];
-        a.cap = gptr(st->cap)[gw];
-        const int32_t peak = gptr(st->peak)[gw];
-        a.loe = gptr(st->peake)[gw];
-        a.base = gptr(st->slot_base)[gw];
-        a.ep = gptr(st->e) + a.base;
-        a.sp = gptr(st->s) + a.base;
-        a.SC = gptr(st->SC)[gw];
-        a.SR = gptr(st->SR)[gw];
-        a.key = gptr(st->key)[gw];
+        const int32_t n = gptr(st->n)[gw], head = gptr(st->head)[gw], cap = gptr(st->cap)[gw];
+        const int32_t M = gptr(st->M)[gw], peak = gptr(st->peak)[gw], loe = gptr(st->peake)[gw];
+        const int64_t base = gptr(st->slot_base)[gw];
+        const uint64_t key = gptr(st->key)[gw];
         const int64_t ds = gptr(st->DS)[gw], s1 = gptr(st->S1)[gw], s2 = gptr(st->S2)[gw];
         const bool cur = gptr(st->hbs)[gw] == hb;
+        double dlim = INFINITY, phi = 0.0;
+        int32_t lgn = 0;
         if (USE_D) {
-            a.dlim = gptr(st->dlim)[gw];
-            a.phi = gptr(st->phi)[gw];
-            a.lgn = gptr(st->lgn)[gw];
+            dlim = gptr(st->dlim)[gw];
+            phi = gptr(st->phi)[gw];
+            lgn = gptr(st->lgn)[gw];
         }
-        a.B = a.n - a.head;
-        a.slack = a.M - peak;
-        a.flo = (int32_t)((uint32_t)a.slack - (uint32_t)a.loe);
-        a.DS = (double)ds * down;
-        a.S1 = cur ? (double)s1 : 0.0;
-        a.S2 = cur ? (double)s2 : 0.0;
-        a.rhs = rhs_of(a.B);
+        a.w = in ? w : a.w;
+        a.B = in ? n - head : a.B;
+        a.room = in ? cap - (n - head) : a.room;
+        a.M = in ? M : a.M;
+        a.slack = in ? M - peak : a.slack;
+        a.loe = in ? loe : a.loe;
+        a.flo = in ? (int32_t)((uint32_t)(M - peak) - (uint32_t)loe) : a.flo;
+        a.key = in ? key : a.key;
+        a.lead = in ? key_lead(key) : a.lead;
+        a.DS = in ? (double)ds * down : a.DS;
+        a.S1 = in ? (cur ? (double)s1 : 0.0) : a.S1;
+        a.S2 = in ? (cur ? (double)s2 : 0.0) : a.S2;
+        a.rhs = in ? rhs_of(n - head) : a.rhs;
+        if (USE_D) a.dlim = in ? dlim : a.dlim;
+        if (in) {
+            L.base[lane] = base;
+            L.rk[lane] = rk;
+            L.head[lane] = head;
+            L.n[lane] = n;
+            L.cap[lane] = cap;
+            if (USE_D) {
+                L.lgn[lane] = lgn;
+                L.phi[lane] = phi;
+            }
+        }
     };
-    // make sure lane j's columns are in the pool
-    auto fetch_columns = [&](int j) {
-        cached = uni(cached);
-        pool_at = uni(pool_at);
-        if (ALD_LIKELY((cached >> j) & 1)) return;
-        const StateArg st = state_arg();
-        const int B = rdlane(a.B, j), tn = rdlane(a.tn, j), head = rdlane(a.head, j), n = rdlane(a.n, j);
-        const int cap = rdlane(a.cap, j);
-        const int64_t base = rdlane64s(a.base, j);
-        const int room = B + POOL_SLACK;
-        if (pool_at + room > POOL) {  // full: every copy is dropped (HBM holds what they were made from)
-            cached = 0;
-            pool_at = 0;
+    // (per lane, within a group) the lane that this lane's query was committed to
+    // (-1: none yet), and the requests its worker held before
+    int32_t rl = -1, rB = 0;
+    // room in the pool for lane j's columns: false if it has to be cleared first
+    auto reserve = [&](int j) ALD_INLINE -> bool {
+        const int room = rdlane(a.B, j) + POOL_SLACK;
+        if (pool_at + room > POOL) return false;
+        if (lane == 0) {
+            L.off[j] = pool_at;
+            L.room[j] = room;
         }
-        const int off = pool_at;
         pool_at += room;
         cached |= 1ull << j;
-        if (lane == j) {
-            a.off = off;
-            a.room = room;
-        }
-        const int B0 = n - head;
-        const int32_t* const ge = gptr(st->e) + base + head;
-        const int32_t* const gs_ = gptr(st->s) + base + head;
-        for (int k0 = 0; k0 < B0; k0 += 4 * NT) {
-            int32_t ve[4], vs[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int k = min(k0 + u * NT + lane, B0 - 1);
-                ve[u] = ge[k];
-                vs[u] = gs_[k];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int k = k0 + u * NT + lane;
-                if (k < B0) {
-                    L.pe[off + k] = ve[u];
-                    L.ps[off + k] = vs[u];
-                }
-            }
-        }
-        wave_sync();
-        if (ALD_RARELY(tn > 0)) {
-            __builtin_amdgcn_s_waitcnt(0);  // this wave's appends have left
-            for (int t = 0; t < tn; ++t) {
-                int p = n + t;
-                p = p > cap ? p - (cap + 1) : p;
-                const int32_t x = coherent(gptr(st->e) + base + p), y = coherent(gptr(st->s) + base + p);
-                lds_sorted_insert(L.pe + off, L.ps + off, B0 + t, x, y);
-            }
-        }
+        return true;
     };
-    // exact KV demand of lane j's worker with the query; the lane's bounds become exact
-    auto scan = [&](int j, int32_t sq, int32_t eq) -> int32_t {
-        fetch_columns(j);
-        const int off = rdlane(a.off, j);
-        const Peak r = wave_kv_peak(L.pe + off, L.ps + off, rdlane(a.B, j), sq, eq);
-        if (lane == j) {
-            a.slack = a.M - r.without;
-            a.loe = r.at;
-            a.flo = a.slack - r.at;
+    // exact KV demand of lane j's worker with the query; the lane's bounds become
+    // exact (lin, lp: the group's queries)
+    auto scan = [&](int j, int32_t sq, int32_t eq, int32_t lin, int32_t lp) ALD_INLINE -> int32_t {
+        cached = uni(cached);
+        pool_at = uni(pool_at);
+        wave_sync();
+        const int B = rdlane(a.B, j);
+        if (ALD_RARELY(!((cached >> j) & 1) || B > uni(L.room[j]))) {
+            if (!reserve(j)) {  // full: every copy is dropped (HBM holds what they were made from)
+                cached = 0;
+                pool_at = 0;
+                reserve(j);
+            }
+            wave_sync();
+            copy_columns(L, j);
         }
+        if (uni(L.have[j]) < B) {
+            __builtin_amdgcn_s_waitcnt(0);  // earlier groups' appends have left
+            advance_columns<DIAG>(L, P.peak, j, B, tau, rl, rB, lin, lp);
+        }
+        const int off = uni(L.off[j]);
+        const Peak r = wave_kv_peak(L.pe + off, L.ps + off, B, sq, eq);
+        const int32_t slack = rdlane(a.M, j) - r.without;
+        a.slack = ald_writelane(slack, j, a.slack);
+        a.loe = ald_writelane(r.at, j, a.loe);
+        a.flo = ald_writelane(slack - r.at, j, a.flo);
         return r.with;
     };
+    // (a changed worker's mark is set when someone looks: a decision only adds its
+    // lane to dm)
+    uint64_t noted = 0;
+    auto note_dirty = [&]() ALD_INLINE {
+        const uint64_t fresh = dm & ~noted;
+        if (fresh != 0) {
+            if (W <= DBITS_W * 32) {
+                if (in_mask(fresh)) atomicOr(&L.dbits[a.w >> 5], 1u << (a.w & 31));
+            } else if (in_mask(dm)) {
+                L.dw[rank_in(dm)] = a.w;
+            }
+            noted = dm;
+            wave_sync();
+        }
+    };
 
-    // short tiles with diagnostics: the commit merges the worker blocks' results
-    // per query itself and writes every query's diagnostics (else the selection
-    // wrote those of the queries that no worker can take)
-    const bool brief = DIAG && state_arg()->brief != 0;
     int pos = brief ? start : fpc;
     // why the tile was cut (0: not)
     constexpr int CUT_STALE = 1, CUT_SLOTS = 2, CUT_PAIR = 3, CUT_LANES = 4;
     int cut = 0;
-    int32_t range = 0;  // (per lane) nonzero: a sum left the exactly representable range
+    int32_t full_w = -1;  // (CUT_SLOTS) the worker without one
     int commits = 0;
     int nrej = pos - start;  // the rejected prefix
     int firstrej = pos > start ? start : INT32_MAX;
@@ -534,24 +766,21 @@ __global__ __launch_bounds__(COMMIT_THREADS) void k_commit(State)
             if (DIAG && !brief) q = gptr(state_arg()->qsum)[scen_arg()->qsum_off + (i - start)];
         }
         if (brief) {
-            const int64_t stride = scen_arg()->pstride;
-            const ulonglong2* row = gptr(state_arg()->part) + scen_arg()->part_off + 2 * (int64_t)(act ? i - start : 0);
             uint64_t a1 = ~0ull, a2 = ~0ull;
-            const int nblk = scen_arg()->nblk;
-#pragma unroll 16
-            for (int b = 0; b < nblk; ++b) {
-                const ulonglong2 x = row[2 * b * stride], y = row[2 * b * stride + 1];
-                merge_two(a1, a2, x.x, x.y);
-                q.nfeas += (int32_t)y.x;
-                q.ntcnt += (int32_t)y.y;
+            for (int v = g * shares; v < (g + 1) * shares; ++v) {
+                const PeakLDS::Two x = P.two[v][lane];
+                merge_two(a1, a2, x.a1, x.a2);
+                q.nfeas += x.nfeas;
+                q.ntcnt += x.ntcnt;
             }
             ex_unpack(a1, q.ex1, q.w1);
             ex_unpack(a2, q.ex2, q.w2);
+            if (!act) q.nfeas = q.ntcnt = 0;
         }
         const double qd = (double)(((int64_t)lin << gs) + (int64_t)scen_arg()->gn * lp) * down;
 
         // the group's bit word of this lane's worker w (all lanes call it)
-        auto word_of = [&](const uint64_t* bits, int w) -> uint64_t {
+        auto word_of = [&](const uint64_t* bits, int w) ALD_INLINE -> uint64_t {
             const uint64_t* col = bits + scen_arg()->bits_off + w;
             if (!sorted) return col[(int64_t)g * W];
             uint64_t r = 0;
@@ -579,17 +808,28 @@ __global__ __launch_bounds__(COMMIT_THREADS) void k_commit(State)
         };
         // the first untouched worker at or after rank r0 whose bit for query t's
         // position is set (-1: none), and its rank
-        auto first_untouched = [&](const uint64_t* bits, int t, int r0, int& fr) -> int {
+        auto first_untouched = [&](const uint64_t* bits, int t, int r0, int& fr) ALD_INLINE -> int {
             const uint64_t* row = bits + scen_arg()->bits_off + (int64_t)(t >> 6) * W;
+            note_dirty();
             const int nd = __popcll(dm);
-            for (; r0 < W; r0 += NT) {
-                const int w = worker_at(min(r0 + lane, W - 1));
-                const uint64_t v = row[bits_at(min(r0 + lane, W - 1))];
-                const uint64_t hit = ballot(r0 + lane < W && ((v >> (t & 63)) & 1) && !dirty_w(L, W, nd, w));
-                if (hit) {
-                    const int l = first_lane(hit);
-                    fr = r0 + l;
-                    return rdlane(w, l);
+            constexpr int U = 4;  // reads in flight
+            for (; r0 < W; r0 += NT * U) {
+                int32_t w[U];
+                uint64_t v[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    w[u] = worker_at(min(r0 + u * NT + lane, W - 1));
+                    v[u] = row[bits_at(min(r0 + u * NT + lane, W - 1))];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const bool in = r0 + u * NT + lane < W;
+                    const uint64_t hit = ballot(in && ((v[u] >> (t & 63)) & 1) && !dirty_w(L, W, nd, w[u]));
+                    if (hit) {
+                        const int l = first_lane(hit);
+                        fr = r0 + u * NT + l;
+                        return rdlane(w[u], l);
+                    }
                 }
             }
             return -1;
@@ -602,6 +842,7 @@ __global__ __launch_bounds__(COMMIT_THREADS) void k_commit(State)
         uint64_t over_key = 0;
         if (potm != 0) {
             const uint64_t* const bits = gptr(state_arg()->bits_feas);
+            note_dirty();
             const int nd = __popcll(dm), nfree = NT - nd;
             int cnt = 0;
             constexpr int U = 4;
@@ -640,16 +881,13 @@ __global__ __launch_bounds__(COMMIT_THREADS) void k_commit(State)
                 over_key = gptr(state_arg()->key)[scen_arg()->wbase + over_w];
             }
             cached &= dm;  // (an untouched worker's columns go with its lane)
-            if (in_mask(~dm)) {
-                const int k = rank_in(~dm);
-                a.w = -1;
-                if (k < min(cnt, nfree)) {
-                    load_slot(L.cw[k], L.cr[k]);
-                    wbf = L.cword[k];
-                }
-            }
+            const int k = rank_in(~dm);
+            const bool pick = in_mask(~dm) && k < min(cnt, nfree);
+            a.w = in_mask(~dm) ? -1 : a.w;
+            load_slot(pick, pick ? L.cw[k] : 0, pick ? L.cr[k] : 0);
+            wbf = pick ? L.cword[k] : 0;
             if (dm != 0) {
-                const uint64_t v = word_of(bits, bits_at(a.rk));
+                const uint64_t v = word_of(bits, bits_at(in_mask(dm) ? L.rk[lane] : 0));
                 if (in_mask(dm)) wbf = v;
             }
         }
@@ -658,90 +896,121 @@ __global__ __launch_bounds__(COMMIT_THREADS) void k_commit(State)
             const uint64_t v = word_of(gptr(state_arg()->bits_nt), max(a.w, 0));
             wbn = a.w >= 0 ? v : 0;
         }
-        // With diagnostics every chosen worker is scanned: the columns of the
-        // best-ranked untouched ones, one per query that can be placed, are read
-        // together (a scan that has to fetch them waits a round trip; without
-        // diagnostics so few are scanned that reading ahead cost more: 72 -> 83 us
-        // per tile of 50 queries over 257 workers whose capacity binds)
-        if (DIAG && potm != 0) {
-            uint64_t want = ~dm & ~cached & ballot(a.w >= 0 && a.B <= 128);
-            for (int k = __popcll(want) - __popcll(potm); k > 0; --k) want &= ~(1ull << (63 - __builtin_clzll(want)));
-            while (want != 0) {
-                constexpr int U = 8;
-                int j[U], off[U];
-                int32_t ve[U][2], vs[U][2];
-                int n = 0;
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    j[u] = want != 0 ? first_lane(want) : j[u > 0 ? u - 1 : 0];
-                    const int room = rdlane(a.B, j[u]) + POOL_SLACK;
-                    const bool fits = want != 0 && pool_at + room <= POOL;
-                    off[u] = pool_at;
-                    if (fits) {
-                        pool_at += room;
-                        cached |= 1ull << j[u];
-                        if (lane == j[u]) {
-                            a.off = off[u];
-                            a.room = room;
-                        }
-                        n = u + 1;
-                    }
-                    want = fits ? want & (want - 1) : 0;
-                    const int B = rdlane(a.B, j[u]), head = rdlane(a.head, j[u]);
-                    const int32_t* ge = (const int32_t*)rdlane64((uint64_t)a.ep, j[u]) + head;
-                    const int32_t* gs_ = (const int32_t*)rdlane64((uint64_t)a.sp, j[u]) + head;
-#pragma unroll
-                    for (int c = 0; c < 2; ++c) {
-                        const int k = max(min(c * 64 + lane, B - 1), 0);
-                        ve[u][c] = gptr(ge)[k];
-                        vs[u][c] = gptr(gs_)[k];
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int B = rdlane(a.B, j[u]);
-#pragma unroll
-                    for (int c = 0; c < 2; ++c)
-                        if (u < n && c * 64 + lane < B) {
-                            L.pe[off[u] + c * 64 + lane] = ve[u][c];
-                            L.ps[off[u] + c * 64 + lane] = vs[u][c];
-                        }
-                }
-            }
-            wave_sync();
-        }
         // (diagnostics) this lane's query's results: as at tile start until its turn
-        int32_t d_feas = q.nfeas, d_near = q.ntcnt > 0 ? 1 : 0, d_peak = 0, d_ex = q.ex1;
-        int32_t d_t0 = 0, d_t1 = 0, d_d0 = 0, d_d1 = 0;  // ttft and tdec of the choice (low and high words)
+        int32_t d_feas = q.nfeas, d_near = q.ntcnt > 0 ? 1 : 0, d_ex = q.ex1;
         // and whether the workers of its two smallest excesses have changed
         int32_t hit1 = 0, hit2 = 0;
         if (DIAG && dm != 0) {
+            note_dirty();
             hit1 = q.w1 >= 0 && dirty_w(L, W, __popcll(dm), q.w1) ? 1 : 0;
             hit2 = q.w2 >= 0 && dirty_w(L, W, __popcll(dm), q.w2) ? 1 : 0;
         }
         // the smallest excess of query p, whose best worker has changed but not the
         // second best
-        auto excess = [&](int p, int32_t sq, int32_t eq) -> int32_t {
+        auto excess = [&](int p, int32_t sq, int32_t eq) ALD_INLINE -> int32_t {
             const int32_t x2 = rdlane(q.ex2, p), w2 = rdlane(q.w2, p);
             const int j = first_lane(dm & ballot(a.w == rdlane(q.w1, p)));
             // (commits only raise a demand: a floor at or above the second smallest
             // leaves that one)
             if (w2 >= 0 && rdlane(a.loe, j) <= eq && (int64_t)sq - rdlane(a.flo, j) >= x2) return x2;
-            const int32_t now = scan(j, sq, eq) - rdlane(a.M, j);
+            const int32_t now = scan(j, sq, eq, lin, lp) - rdlane(a.M, j);
             stale += 1;
             return (w2 < 0 || now < x2) ? now : x2;
         };
 
-        int32_t res = -1;  // this lane's query's worker
+        rl = -1;
         int lim = NT;      // queries of lanes below lim are decided when the group ends (the tile is cut there)
         // queries left to decide (with diagnostics, once a worker has changed,
         // the rejected ones too)
         uint64_t todo = (DIAG && dm != 0) ? actm : potm;
+        const uint64_t nearm = DIAG ? ballot(q.ntcnt > 0) : 0;
         while (uni(todo) != 0) {
             todo = uni(todo);
             dm = uni(dm);
             cached = uni(cached);
             stale = uni(stale);
+            // ---- the decisions that need no scan, no look at the workers beyond the
+            // lanes and no tie rule: one straight block per decision, left at the
+            // first query that does
+            if (ALD_LIKELY(stale < STALE_CUT) && (!DIAG || dm != 0)) {
+                const uint32_t over_lead = key_lead(over_key);
+                uint64_t t = todo;
+                uint64_t hitm = DIAG ? ballot(hit1 != 0) | nearm : 0;
+                do {
+                    const int p = first_lane(t);
+                    const int32_t plin = rdlane(lin, p), plp = rdlane(lp, p);
+                    const double pqd = rdlane_f64(qd, p), dlin = (double)plin;
+                    const int32_t eq = plp + tau, sq = plin - tau;
+                    // this lane's worker with the query added: (b), then (c) and (d)
+                    const double DS = a.DS + pqd, S1 = a.S1 + dlin, S2 = a.S2 + dlin * dlin;
+                    const double lhs = k2 * DS, tt = (c1 + k1 * S1) + k1q * S2;
+                    const uint64_t fsm = ballot((wbf >> p) & 1);
+                    uint64_t cand = fsm & ballot(lhs <= a.rhs) & ballot(tt <= ttft);
+                    if (USE_D) cand &= ballot(a.dlim == INFINITY || tt <= a.dlim);
+                    // (changed workers: surely feasible, surely not, or to be scanned)
+                    cand &= ~(dm & ballot(a.loe <= eq) & ballot(sq > a.flo));
+                    const uint64_t unsure = dm & ~ballot(plin + plp <= a.slack);
+                    // the best rank by the keys' leading bits; among equal ones the first
+                    // lane if all are untouched (these are in rank order)
+                    const uint32_t top = wave_max_u32(in_mask(cand) ? a.lead : 0u);
+                    const uint64_t m = cand & ballot(a.lead == top);
+                    const uint64_t bit = m & (0 - m);
+                    bool rare = (m == 0) | (((m ^ bit) != 0) & ((m & dm) != 0)) | (over & (top <= over_lead));
+                    rare = rare | (((DIAG ? cand : bit) & unsure) != 0) | ((bit & ballot(a.room <= 0)) != 0);
+                    if (DIAG) {
+                        uint64_t tied = ballot(near_tie(lhs, a.rhs)) | (ballot(ttft != INFINITY) & ballot(near_tie(tt, ttft)));
+                        if (USE_D) tied |= ballot(a.dlim != INFINITY) & ballot(near_tie(tt, a.dlim));
+                        // (a rejected query is looked at in the slow path too)
+                        rare = rare | ((tied & dm) != 0) | (((hitm >> p) & 1) != 0);
+                    }
+                    if (ALD_RARELY(rare)) break;
+                    const int bl = first_lane(bit);
+                    const int32_t B0 = rdlane(a.B, bl);
+                    const bool sel = in_mask(bit);
+                    if (DIAG) {
+                        const int more = __popcll(dm & cand) - __popcll(dm & fsm);
+                        d_feas = ald_writelane(rdlane(d_feas, p) + more, p, d_feas);
+                        const double td = (c3 + c2 * (double)(B0 + 1)) + lhs;
+                        if (sel) {
+                            P.tt[p] = tt;
+                            P.td[p] = td;
+                        }
+                        const int32_t bw = rdlane(a.w, bl);
+                        hitm |= ballot(q.w1 == bw);
+                        hit1 |= q.w1 == bw ? 1 : 0;
+                        hit2 |= q.w2 == bw ? 1 : 0;
+                    }
+                    dm |= bit;
+                    rl = ald_writelane(bl, p, rl);
+                    rB = ald_writelane(B0, p, rB);
+                    // (B <= 8192, gs <= 8; a sum beyond the range fails the call)
+                    const uint32_t X = (uint32_t)(B0 + 1) << gs, D = (uint32_t)(DS * up);
+                    a.B += sel ? 1 : 0;
+                    a.room -= sel ? 1 : 0;
+                    a.slack -= sel ? plin + plp : 0;
+                    a.flo -= sel && a.loe <= eq ? sq + a.loe : 0;
+                    a.DS = sel ? DS : a.DS;
+                    const uint64_t key = (uint64_t)X * X + (uint64_t)D * D;
+                    a.key = sel ? key : a.key;
+                    a.lead = sel ? key_lead(key) : a.lead;
+                    a.rhs = sel ? rhs_of(B0 + 1) : a.rhs;
+                    a.S1 = sel ? S1 : a.S1;
+                    a.S2 = sel ? S2 : a.S2;
+                    t = uni(t & (t - 1));
+                    if (ALD_RARELY(dm == ~0ull)) break;
+                } while (t != 0);
+                todo = uni(t);
+                dm = uni(dm);
+                if (ALD_RARELY(dm == ~0ull)) {  // every lane holds a changed worker
+                    const int past = 64 - __builtin_clzll(ballot(rl >= 0));  // the last one placed made it so
+                    if (w0 + past < end) {
+                        cut = CUT_LANES;
+                        lim = past;
+                        todo = 0;
+                    }
+                }
+                if (todo == 0) continue;
+            }
             const int p = first_lane(todo);
             if (ALD_RARELY(stale >= STALE_CUT)) {
                 lim = p;
@@ -807,12 +1076,12 @@ __global__ __launch_bounds__(COMMIT_THREADS) void k_commit(State)
             if (!DIAG) {
                 while (ALD_LIKELY(uni(cand) != 0)) {
                     cand = uni(cand);
-                    const int j = best_lane(cand, a.key, a.w);
+                    const int j = best_lane(cand, a.lead, a.key, a.w);
                     if (ALD_LIKELY((sure >> j) & 1)) {
                         bl = j;
                         break;
                     }
-                    const int32_t v = scan(j, sq, eq);
+                    const int32_t v = scan(j, sq, eq, lin, lp);
                     if (v <= rdlane(a.M, j)) {
                         bl = j;
                         pk = v;
@@ -824,12 +1093,12 @@ __global__ __launch_bounds__(COMMIT_THREADS) void k_commit(State)
             } else {
                 for (uint64_t u = cand & ~sure; u != 0; u &= u - 1) {
                     const int j = first_lane(u);
-                    if (scan(j, sq, eq) > rdlane(a.M, j)) {
+                    if (scan(j, sq, eq, lin, lp) > rdlane(a.M, j)) {
                         cand &= ~(1ull << j);
                         stale += 1;
                     }
                 }
-                if (cand != 0) bl = best_lane(cand, a.key, a.w);
+                if (cand != 0) bl = best_lane(cand, a.lead, a.key, a.w);
             }
             bl = uni(bl);
             pk = uni(pk);
@@ -844,16 +1113,14 @@ __global__ __launch_bounds__(COMMIT_THREADS) void k_commit(State)
                     // is then the best one beyond the lanes
                     const int l = 63 - __builtin_clzll(~dm);
                     over_w = rdlane(a.w, l);
-                    over_r = rdlane(a.rk, l);
+                    over_r = uni(L.rk[l]);
                     over_key = rdlane64(a.key, l);
                     cached &= ~(1ull << l);
                     const uint64_t vf = word_of(gptr(state_arg()->bits_feas), bits_at(fr));
                     const uint64_t vn = DIAG ? word_of(gptr(state_arg()->bits_nt), fw) : 0;
-                    if (lane == l) {
-                        load_slot(fw, fr);
-                        wbf = vf;
-                        wbn = vn;
-                    }
+                    load_slot(lane == l, fw, fr);
+                    wbf = lane == l ? vf : wbf;
+                    if (DIAG) wbn = lane == l ? vn : wbn;
                     if (DIAG) {
                         lhs = k2 * (a.DS + pqd);
                         tt = (c1 + k1 * (a.S1 + dlin)) + k1q * (a.S2 + dlin * dlin);
@@ -896,15 +1163,11 @@ __global__ __launch_bounds__(COMMIT_THREADS) void k_commit(State)
                 }
                 d_near = ald_writelane(nt ? 1 : 0, p, d_near);
                 if (bl >= 0) {
-                    pk = scan(bl, sq, eq);
-                    d_peak = ald_writelane(pk, p, d_peak);
                     const double td = (c3 + c2 * (double)(a.B + 1)) + lhs;
-                    const uint64_t t = rdlane64(__builtin_bit_cast(uint64_t, tt), bl);
-                    const uint64_t d = rdlane64(__builtin_bit_cast(uint64_t, td), bl);
-                    d_t0 = ald_writelane((int32_t)(uint32_t)t, p, d_t0);
-                    d_t1 = ald_writelane((int32_t)(uint32_t)(t >> 32), p, d_t1);
-                    d_d0 = ald_writelane((int32_t)(uint32_t)d, p, d_d0);
-                    d_d1 = ald_writelane((int32_t)(uint32_t)(d >> 32), p, d_d1);
+                    if (lane == bl) {
+                        P.tt[p] = tt;
+                        P.td[p] = td;
+                    }
                 }
             }
             if (ALD_RARELY(bl < 0)) {
@@ -912,67 +1175,42 @@ __global__ __launch_bounds__(COMMIT_THREADS) void k_commit(State)
                 continue;
             }
 
-            // ---- commit the query to lane bl's worker
-            if (lane == p) res = bw;
-            if (ALD_RARELY(!((ballot(a.B < a.cap) >> bl) & 1))) {  // no slot left for one more live request
+            // ---- commit the query to lane bl's worker (its request and the sums of c
+            // and r are stored when the group ends: a store here would be waited
+            // for at the next decision's first load)
+            const int32_t B0 = rdlane(a.B, bl);
+            if (ALD_RARELY(rdlane(a.room, bl) <= 0)) {  // no slot left for one more live request
+                full_w = bw;
                 cut = CUT_SLOTS;
                 lim = p + 1;
                 todo = 0;
                 continue;
             }
-            if (ALD_RARELY(!((dm >> bl) & 1))) {  // untouched so far
-                if (lane == 0) {
-                    L.dw[__popcll(dm)] = bw;
-                    if (W <= DBITS_W * 32) L.dbits[bw >> 5] |= 1u << (bw & 31);
-                }
-                dm |= 1ull << bl;
-                wave_sync();
-                if (DIAG) {  // from here on the rejected queries are looked at too
-                    todo = actm & (~0ull << p) & ~(1ull << p);
-                    hit1 |= q.w1 == bw ? 1 : 0;
-                    hit2 |= q.w2 == bw ? 1 : 0;
-                }
+            if (DIAG) {
+                // once a worker has changed the rejected queries are looked at too
+                if (dm == 0) todo = actm & (~0ull << p) & ~(1ull << p);
+                hit1 |= q.w1 == bw ? 1 : 0;
+                hit2 |= q.w2 == bw ? 1 : 0;
             }
-            if (DIAG ? ALD_LIKELY((cached >> bl) & 1) : ALD_RARELY((cached >> bl) & 1)) {
-                const int B0 = rdlane(a.B, bl);
-                if (ALD_LIKELY(B0 < rdlane(a.room, bl))) {
-                    const int off = rdlane(a.off, bl);
-                    lds_sorted_insert(L.pe + off, L.ps + off, B0, eq, sq);
-                } else {
-                    cached &= ~(1ull << bl);
-                }
-            }
-            if (lane == bl) {
-                // behind the sorted columns (in the room of finished requests
-                // where the slot range ends)
-                int at = a.n + a.tn;
-                at = at > a.cap ? at - (a.cap + 1) : at;
-                a.ep[at] = eq;
-                a.sp[at] = sq;
-                a.tn += 1;
-                a.B += 1;
-                a.SC += plin;
-                a.SR += plp;
-                a.DS += pqd;
-                const double DS = a.DS * up;
-                range |= DS >= 0x1p31 ? 1 : 0;
-                const uint32_t X = (uint32_t)a.B << gs, D = (uint32_t)DS;  // (B <= 8192, gs <= 8)
-                a.key = (uint64_t)X * X + (uint64_t)D * D;
-                a.rhs = rhs_of(a.B);
-                a.S1 += dlin;
-                a.S2 += dlin * dlin;
-                range |= a.S2 >= 0x1p53 ? 1 : 0;
-                a.slack = pk >= 0 ? a.M - pk : a.slack - (plin + plp);
-                if (a.loe <= eq) a.flo -= sq + a.loe;
-                if (USE_D) {
-                    // the new request decodes from the end of this heartbeat with zero slack
-                    const StateArg st = state_arg();
-                    const int64_t lpos = a.base + a.lgn;
-                    gptr(st->lge)[lpos] = eq;
-                    gptr(st->lgw)[lpos] = hb;
-                    gptr(st->lgs)[lpos] = -a.phi;
-                    a.lgn += 1;
-                }
+            dm |= 1ull << bl;
+            rl = ald_writelane(bl, p, rl);
+            rB = ald_writelane(B0, p, rB);
+            {
+                const bool sel = lane == bl;
+                const double DS = a.DS + pqd;
+                // (B <= 8192, gs <= 8; a sum beyond the range fails the call)
+                const uint32_t X = (uint32_t)(B0 + 1) << gs, D = (uint32_t)(DS * up);
+                a.B += sel ? 1 : 0;
+                a.room -= sel ? 1 : 0;
+                a.slack = sel ? (pk >= 0 ? a.M - pk : a.slack - (plin + plp)) : a.slack;
+                a.flo -= sel && a.loe <= eq ? sq + a.loe : 0;
+                a.DS = sel ? DS : a.DS;
+                const uint64_t key = (uint64_t)X * X + (uint64_t)D * D;
+                a.key = sel ? key : a.key;
+                a.lead = sel ? key_lead(key) : a.lead;
+                a.rhs = sel ? rhs_of(B0 + 1) : a.rhs;
+                a.S1 = sel ? a.S1 + dlin : a.S1;
+                a.S2 = sel ? a.S2 + dlin * dlin : a.S2;
             }
             if (ALD_RARELY(dm == ~0ull) && w0 + p + 1 < end) {  // every lane holds a changed worker
                 cut = CUT_LANES;
@@ -984,6 +1222,69 @@ __global__ __launch_bounds__(COMMIT_THREADS) void k_commit(State)
         cut = uni(cut);
         // the group's outputs and rejections
         const uint64_t donem = actm & (lim >= NT ? ~0ull : ((1ull << lim) - 1));
+        if (DIAG) {
+            // the peaks of the placements that no scan computed on its way
+            uint64_t left = 0;
+            for (uint64_t m = ballot(rl >= 0); m != 0; m &= ~ballot(rl == rdlane(rl, first_lane(m))))
+                left |= 1ull << rdlane(rl, first_lane(m));
+            wave_sync();
+            left &= ~(cached & ballot(L.have[lane] >= a.B));
+            if (left != 0) {
+                P.rl[lane] = rl;
+                P.rB[lane] = rB;
+                P.lin[lane] = lin;
+                P.lp[lane] = lp;
+                P.B[lane] = a.B;
+            }
+            while (uni(left) != 0) {
+                left = uni(left);
+                cached = uni(cached);
+                pool_at = uni(pool_at);
+                uint64_t jobs = left & cached & ballot(a.B <= L.room[lane]), fetch = 0;
+                for (uint64_t m = left & ~jobs; m != 0; m &= m - 1) {
+                    const int j = first_lane(m);
+                    if (!reserve(j)) break;
+                    fetch |= 1ull << j;
+                }
+                jobs |= fetch;
+                if (jobs == 0) {  // full: every copy is dropped (HBM holds what they were made from)
+                    cached = 0;
+                    pool_at = 0;
+                    continue;
+                }
+                if (lane == 0) {
+                    P.jobs = jobs;
+                    P.fetch = fetch;
+                }
+                __syncthreads();
+                run_jobs(L, P, 0, tau);
+                __syncthreads();
+                if (in_mask(jobs)) a.slack = a.M - P.last[lane];
+                left &= ~jobs;
+            }
+        }
+        const int32_t on = __shfl(a.w, max(rl, 0), 64);
+        const int32_t res = rl >= 0 ? on : (cut == CUT_SLOTS && lane == lim - 1 ? full_w : -1);
+        if (rl >= 0) {
+            // the request goes behind the worker's sorted columns (in the room of
+            // finished requests where the slot range ends)
+            const StateArg st = state_arg();
+            const int64_t base = L.base[rl];
+            const int32_t cap = L.cap[rl], head = L.head[rl];
+            int at = head + rB;
+            at = at > cap ? at - (cap + 1) : at;
+            gptr(st->e)[base + at] = lp + tau;
+            gptr(st->s)[base + at] = lin - tau;
+            atomicAdd((unsigned long long*)&L.dsc[rl], (unsigned long long)lin);
+            atomicAdd((unsigned long long*)&L.dsr[rl], (unsigned long long)lp);
+            if (USE_D) {
+                // it decodes from the end of this heartbeat with zero slack
+                const int64_t lpos = base + L.lgn[rl] + (rB - (L.n[rl] - head));
+                gptr(st->lge)[lpos] = lp + tau;
+                gptr(st->lgw)[lpos] = hb;
+                gptr(st->lgs)[lpos] = -L.phi[rl];
+            }
+        }
         if (in_mask(donem)) {
             const int64_t k = q_index(i);
             if (out != nullptr) out[k] = res < 0 ? res : res + scen_arg()->out_add;
@@ -991,10 +1292,10 @@ __global__ __launch_bounds__(COMMIT_THREADS) void k_commit(State)
                 Diag d;
                 d.n_feasible = d_feas;
                 d.near_tie = d_near;
-                d.kv_peak_chosen = d_peak;
+                d.kv_peak_chosen = rl >= 0 ? P.peak[lane] : 0;
                 d.kv_excess_min = d_ex;
-                d.ttft_chosen = __builtin_bit_cast(double, ((uint64_t)(uint32_t)d_t1 << 32) | (uint32_t)d_t0);
-                d.tdec_chosen = __builtin_bit_cast(double, ((uint64_t)(uint32_t)d_d1 << 32) | (uint32_t)d_d0);
+                d.ttft_chosen = rl >= 0 ? P.tt[lane] : 0.0;
+                d.tdec_chosen = rl >= 0 ? P.td[lane] : 0.0;
                 gptr(state_arg()->out_diag)[k] = d;
             }
         }
@@ -1004,22 +1305,31 @@ __global__ __launch_bounds__(COMMIT_THREADS) void k_commit(State)
         if (rm && firstrej == INT32_MAX) firstrej = w0 + first_lane(rm);
         pos = min(end, w0 + lim);
     }
+    if (NWV > 1) {
+        if (lane == 0) P.jobs = 0;
+        __syncthreads();  // the other waves are done
+    }
     // write back the changed workers' sums and list the workers whose summaries
     // the next round must rebuild
     const StateArg st = state_arg();
+    bool range = false;  // a sum left the exactly representable range (they only grow)
+    wave_sync();
     if (in_mask(dm)) {
         const int gw = scen_arg()->wbase + a.w;
-        gptr(st->tn)[gw] = a.tn;
+        range = a.DS * up >= 0x1p31 || a.S2 >= 0x1p53;
+        const int tn = a.B - (L.n[lane] - L.head[lane]);
+        const int64_t SC = gptr(st->SC)[gw] + (int64_t)L.dsc[lane], SR = gptr(st->SR)[gw] + (int64_t)L.dsr[lane];
+        gptr(st->tn)[gw] = tn;
         gptr(st->B)[gw] = a.B;
-        gptr(st->SC)[gw] = a.SC;
-        gptr(st->SR)[gw] = a.SR;
-        gptr(st->DS)[gw] = (a.SC << gs) + (int64_t)scen_arg()->gn * a.SR;
+        gptr(st->SC)[gw] = SC;
+        gptr(st->SR)[gw] = SR;
+        gptr(st->DS)[gw] = (SC << gs) + (int64_t)scen_arg()->gn * SR;
         gptr(st->key)[gw] = a.key;
         gptr(st->rhs)[gw] = a.rhs;
         gptr(st->S1)[gw] = (int64_t)a.S1;
         gptr(st->S2)[gw] = (int64_t)a.S2;
         gptr(st->hbs)[gw] = hb;
-        if (USE_D) gptr(st->lgn)[gw] = a.lgn;
+        if (USE_D) gptr(st->lgn)[gw] = L.lgn[lane] + tn;
         gptr(st->built)[gw] = 0;
         gptr(st->dlist)[blockIdx.x * MAX_DIRTY + rank_in(dm)] = gw;
     }
@@ -1040,7 +1350,7 @@ __global__ __launch_bounds__(COMMIT_THREADS) void k_commit(State)
             }
         }
     }
-    const bool ranged = ballot(range != 0) != 0;
+    const bool ranged = ballot(range) != 0;
     const int nd = __popcll(dm);
     if (lane == 0) {
         Ctl o = c;

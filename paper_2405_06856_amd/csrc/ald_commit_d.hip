@@ -5,9 +5,12 @@ namespace ald {
 
 hipError_t launch_commit_d(const State& st, int32_t blocks, hipStream_t stream)
 {
-    const dim3 g(blocks), b(COMMIT_THREADS);
-    if (st.out_diag != nullptr) hipLaunchKernelGGL((k_commit<true, true>), g, b, 0, stream, st);
-    else hipLaunchKernelGGL((k_commit<false, true>), g, b, 0, stream, st);
+    const dim3 g(blocks);
+    if (st.out_diag != nullptr) {
+        hipLaunchKernelGGL((k_commit<true, true>), g, dim3(COMMIT_THREADS * commit_waves(true)), 0, stream, st);
+    } else {
+        hipLaunchKernelGGL((k_commit<false, true>), g, dim3(COMMIT_THREADS * commit_waves(false)), 0, stream, st);
+    }
     return hipGetLastError();
 }
 
