@@ -44,7 +44,7 @@ constexpr int POOL = 12800;     // pool entries (8 B each) for changed workers' 
 constexpr int POOL_SLACK = 48;  // entries a copied worker may grow by before it is copied again
 static_assert(POOL >= HOT + POOL_SLACK, "the largest worker fits the pool");
 
-// Orders LDS traffic between the lanes of the (single-wave) commit block
+// Orders LDS traffic between the lanes of one wave of the commit block
 // without waiting for outstanding global memory operations.
 __device__ __forceinline__ void wave_sync() { __builtin_amdgcn_wave_barrier(); }
 

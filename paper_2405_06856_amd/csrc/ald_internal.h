@@ -44,7 +44,7 @@ constexpr int SHORT_WPB = 64;      // workers per block of it at most
 constexpr int SHORT_STAGE = 256;   // it searches the ends of workers with fewer live requests in LDS
 constexpr int SMALL_SLOTS = 512;   // workers of at most this many request slots are built by one wave
 constexpr int SEL_THREADS = 256;   // queries per selection block
-constexpr int COMMIT_THREADS = 64;  // the arrival-order commit runs as one wave
+constexpr int COMMIT_THREADS = 64;  // the arrival-order commit decides in one wave
 constexpr int HOT = 8192;          // most request slots per worker (the commit can hold one such worker in LDS)
 constexpr int BUILD_THREADS = 256;
 constexpr int MAX_DIRTY = 64;      // workers changed within one tile before the tile is cut
